@@ -697,17 +697,21 @@ struct RowArgs {
   const double* lb_q;
   int variant;  // batched launches: this instance's tile variant (0 or 2)
   const double* scal;  // ROW_GRAD_STEP: device scalars (the step length)
+  // plane passes (plane_body): rows per x plane, x planes, y twiddles
+  int ny, nplanes;
+  const cx<T>* tw_y;
 };
 
 // The likelihood terms of the gradient at one cell (sections 2.1 and 2.4,
 // the power-law bias; the Gaussian-prior model of section 2.2.2): writes s,
 // e and the Hessian diagonal d, adds to the partial sums (the likelihood
-// part of f, sum d) and returns the likelihood gradient l.
-template <typename T>
+// part of f, sum d) and returns the likelihood gradient l.  GAUSS: whether
+// the Gaussian model may be asked for.
+template <typename T, bool GAUSS>
 __device__ __forceinline__ double grad_cell(const RowArgs<T>& a, long i, double s, double* acc) {
   const double cnt = a.counts[i];
   a.s_out[i] = s;
-  if (a.model == MODEL_GAUSSIAN) {
+  if (GAUSS && a.model == MODEL_GAUSSIAN) {
     // Gaussian prior on delta = s, unity bias:
     // -ln L = sum nbar w (1 + delta) - N ln(1 + delta) + const
     const double nw = a.nbar * a.w[i], op = 1.0 + s;
@@ -737,30 +741,54 @@ struct RowShape {
   static constexpr int LEN = PaddedLen<N + 2, true>::value;  // LDS slots per pair
 };
 
-template <typename T, int N, int OP, int V = 0>
-__device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>* lds_all, int block_linear) {
+// The Hessian diagonal at real cell i, in the transforms' precision.
+template <typename T>
+__device__ __forceinline__ T diag_at(const RowArgs<T>& a, long i, int nt) {
+  if constexpr (sizeof(T) == 8)
+    return ld_stream(a.d + i, nt);
+  else
+    return ld_stream(a.d32 + i, nt);
+}
+
+// How the threads of a row pair transform: exchanges through the padded LDS
+// rows of a row pass, the whole workgroup meeting at barriers.
+template <typename T, int N>
+struct BlockRowFft {
+  using PL = Plan<N>;
+  using MAP = LdsMap<1, true>;
+  static constexpr bool PRELOAD_D = true, STREAM = true, GAUSS = true;
+  int t;
+  cx<T>* lds;
+  const cx<T>* tw;
+  bool active;
+  template <bool INV>
+  __device__ __forceinline__ void fft(cx<T>* v) const { fft_thread<PL, INV, MAP>(v, t, lds, tw, active); }
+  __device__ __forceinline__ void turn(cx<T>* v) const { last_to_first<PL, MAP>(v, t, lds, active); }
+  __device__ __forceinline__ void chunk(int) const {}
+  __device__ __forceinline__ void pin(double (&)[2]) const {}
+};
+
+// One row pair's z transforms and pointwise work: thread t of the Plan<N>::P
+// sharing the pair; rowA, rowB: the two real rows; srcA / dst: the pair's
+// half rows (two rows of H values).  acc: the thread's partial sums.
+template <typename T, int N, int OP, class FX>
+__device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, const int t, const bool active,
+                                         const bool valid, const long rowA, const long rowB, const cx<T>* srcA,
+                                         cx<T>* dst, double (&acc)[2]) {
   using PL = Plan<N>;
   constexpr int P = PL::P;
   constexpr int W = PL::W;
   constexpr int R0 = PL::R0;
   constexpr int RL = LastStage<PL>::R;
-  constexpr int G = RowShape<N, V>::G;
-  constexpr int LEN = RowShape<N, V>::LEN;
   constexpr int H = N / 2 + 1;
-  using MAP = LdsMap<1, true>;
 
-  const bool active = (int)threadIdx.x < RowShape<N, V>::THREADS;
-  const int t = threadIdx.x % P;
-  const int ul = active ? (int)threadIdx.x / P : 0;
-  const int u = ublock * G + ul;
-  const bool valid = active && u < a.nunits;
-  const int uc = valid ? u : 0;
-  cx<T>* lds = lds_all + ul * LEN;
-  const long rowA = 2L * uc, rowB = 2L * uc + 1;
-
+  // Pairs that are not valid stand at a valid pair's addresses: their loads
+  // are unconditional (a branch around each would end the basic block the
+  // loads are scheduled in) and what they load is not used.
   cx<T> v[W];
-  double acc[2] = {0.0, 0.0};
-
+  // (no runtime choice where FX::STREAM is off: its branch would group the
+  // loads of all elements on one side of it)
+  const int nt_d = FX::STREAM ? a.nt & NT_DIAG : 0;
   // ---- gather the complex length-N input Z = A + i B (stage-0 slots) ----
   if constexpr (OP == ROW_GRAD_STEP) {
     // real rows of the stepped iterate: the likelihood gradient l at each
@@ -776,10 +804,12 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const long i = (h ? rowB : rowA) * N + e;
-            l[h] = grad_cell(a, i, a.s_in[i] + al * (double)a.v[i], acc);
+            l[h] = grad_cell<T, FX::GAUSS>(a, i, a.s_in[i] + al * (double)a.v[i], acc);
           }
         }
         v[q * R0 + r] = {(T)l[0], (T)l[1]};
+        fx.chunk(3);
+        fx.pin(acc);
       }
   } else if constexpr (OP == ROW_R2C) {
 #pragma unroll
@@ -787,14 +817,14 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
 #pragma unroll
       for (int r = 0; r < R0; ++r) {
         int e = in_pos<PL, 0>(t, q, r);
-        v[q * R0 + r] = valid ? cx<T>{a.in_r[rowA * N + e], a.in_r[rowB * N + e]} : cx<T>{T(0), T(0)};
+        const T ra = a.in_r[rowA * N + e], rb = a.in_r[rowB * N + e];
+        v[q * R0 + r] = {valid ? ra : T(0), valid ? rb : T(0)};
       }
   } else {
     // the two half rows A (at rowA * H) and B (next H values) give
     // Z[e] = A[e] + i B[e], with A[e] = conj A[N - e] above N/2: each lane
     // loads its elements straight from memory (the lanes of a row pair read
     // consecutive, or mirrored consecutive, values)
-    const cx<T>* srcA = a.in_c + rowA * H;
     const cx<T>* srcB = srcA + H;
 #pragma unroll
     for (int q = 0; q < W / R0; ++q)
@@ -811,34 +841,30 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
           A.y = T(0);
           Bv.y = T(0);
         }
-        v[q * R0 + r] = valid ? cx<T>{A.x - Bv.y, A.y + Bv.x} : cx<T>{T(0), T(0)};
+        v[q * R0 + r] = {valid ? A.x - Bv.y : T(0), valid ? A.y + Bv.x : T(0)};
+        fx.chunk(q * R0 + r);
       }
   }
 
   // ROW_HVP / ROW_LB_IN: the diagonal at the positions this thread
   // multiplies, loaded before the transforms so that its latency overlaps them
-  constexpr bool PRE_D = OP == ROW_HVP || OP == ROW_LB_IN;
+  constexpr bool PRE_D = (OP == ROW_HVP || OP == ROW_LB_IN) && FX::PRELOAD_D;
   T pre_dA[PRE_D ? W : 1], pre_dB[PRE_D ? W : 1];
   if constexpr (PRE_D) {
 #pragma unroll
     for (int q = 0; q < W / RL; ++q)
 #pragma unroll
       for (int m = 0; m < RL; ++m) {
-        int e = out_pos<PL, PL::NS - 1>(t, q, m);
-        if constexpr (sizeof(T) == 8) {
-          pre_dA[q * RL + m] = valid ? (T)ld_stream(a.d + rowA * N + e, a.nt & NT_DIAG) : T(0);
-          pre_dB[q * RL + m] = valid ? (T)ld_stream(a.d + rowB * N + e, a.nt & NT_DIAG) : T(0);
-        } else {
-          pre_dA[q * RL + m] = valid ? ld_stream(a.d32 + rowA * N + e, a.nt & NT_DIAG) : T(0);
-          pre_dB[q * RL + m] = valid ? ld_stream(a.d32 + rowB * N + e, a.nt & NT_DIAG) : T(0);
-        }
+        const int e = active ? out_pos<PL, PL::NS - 1>(t, q, m) : 0;
+        pre_dA[q * RL + m] = diag_at<T>(a, rowA * N + e, nt_d);
+        pre_dB[q * RL + m] = diag_at<T>(a, rowB * N + e, nt_d);
       }
   }
 
   if constexpr (OP == ROW_R2C || OP == ROW_GRAD_STEP) {
-    fft_thread<PL, false, MAP>(v, t, lds, a.tw, active);
+    fx.template fft<false>(v);
   } else {
-    fft_thread<PL, true, MAP>(v, t, lds, a.tw, active);
+    fx.template fft<true>(v);
     // v now holds z[e] = a[e] + i b[e] at last-stage slots (unscaled)
     if constexpr (OP == ROW_C2R) {
       if (valid) {
@@ -888,9 +914,10 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
               a.d_out[i] = a.beta * a.beta * ex;
               acc[0] += ex - a.beta * cnt * s;
             }
+            fx.chunk(3);
+            fx.pin(acc);
           }
       }
-      block_reduce_store<2>(acc, a.partials, block_linear);
       return;
     } else {
       // pointwise work on the real values, then back to half spectra
@@ -899,11 +926,22 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
         for (int q = 0; q < W / RL; ++q)
 #pragma unroll
           for (int m = 0; m < RL; ++m) {
-            const T dA = pre_dA[q * RL + m], dB = pre_dB[q * RL + m];
+            T dA, dB;
+            if constexpr (PRE_D) {
+              dA = pre_dA[q * RL + m];
+              dB = pre_dB[q * RL + m];
+            } else {
+              const int e = out_pos<PL, PL::NS - 1>(t, q, m);
+              dA = diag_at<T>(a, rowA * N + e, nt_d);
+              dB = diag_at<T>(a, rowB * N + e, nt_d);
+            }
+            dA = valid ? dA : T(0);
+            dB = valid ? dB : T(0);
             cx<T> z = v[q * RL + m];
             T va = z.x * a.scale, vb = z.y * a.scale;
             acc[0] += (double)dA * va * va + (double)dB * vb * vb;
             v[q * RL + m] = {va * dA, vb * dB};
+            fx.chunk(q * RL + m);
           }
       } else if constexpr (OP == ROW_LB_IN) {
         // keep q = F^-1 p (real) for the output pass, go on with d q;
@@ -920,7 +958,15 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
               a.out_r[rowB * N + e] = vb;
               acc[0] += a.lb_d1[rowA * N + e] * (double)va * va + a.lb_d1[rowB * N + e] * (double)vb * vb;
             }
-            v[q * RL + m] = {va * pre_dA[q * RL + m], vb * pre_dB[q * RL + m]};
+            T dA, dB;
+            if constexpr (PRE_D) {
+              dA = pre_dA[q * RL + m];
+              dB = pre_dB[q * RL + m];
+            } else {
+              dA = diag_at<T>(a, rowA * N + e, nt_d);
+              dB = diag_at<T>(a, rowB * N + e, nt_d);
+            }
+            v[q * RL + m] = {va * dA, vb * dB};
           }
       } else if constexpr (OP == ROW_LB_OUT) {
         // d g + d1 q at each real position
@@ -940,6 +986,7 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
               }
             }
             v[q * RL + m] = {o[0], o[1]};
+            fx.chunk(q * RL + m);
           }
       } else {  // ROW_GRAD (double only)
 #pragma unroll
@@ -953,14 +1000,19 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
                 long i = (h ? rowB : rowA) * N + e;
-                l[h] = grad_cell(a, i, (double)(h ? z.y : z.x) * (double)a.scale, acc);
+                l[h] = grad_cell<T, FX::GAUSS>(a, i, (double)(h ? z.y : z.x) * (double)a.scale, acc);
               }
             }
             v[q * RL + m] = {(T)l[0], (T)l[1]};
+            fx.chunk(3);
+            fx.pin(acc);
           }
       }
-      last_to_first<PL, MAP>(v, t, lds, active);
-      fft_thread<PL, false, MAP>(v, t, lds, a.tw, active);
+      // the sums so far, now: they are used last, and left to the end they
+      // would keep every operand in registers through the second transform
+      asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
+      fx.turn(v);
+      fx.template fft<false>(v);
     }
   }
 
@@ -974,7 +1026,6 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
   // shuffles (uniform control flow); only valid ones store.
   {
     constexpr int QL = W / RL;
-    cx<T>* dst = a.out_c + rowA * H;
     const int lane = (int)(threadIdx.x & 63);
     const int src_lane = (lane & ~(P - 1)) | ((P - t) & (P - 1));
 #pragma unroll
@@ -996,10 +1047,35 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
         dst[k] = {T(0.5) * (zk.x + zc.x), T(0.5) * (zk.y - zc.y)};
         dst[H + k] = {T(0.5) * (zk.y + zc.y), T(0.5) * (zc.x - zk.x)};
       }
+      fx.chunk(j);
     }
   }
-  if constexpr (OP == ROW_GRAD || OP == ROW_GRAD_STEP || OP == ROW_HVP || OP == ROW_LB_IN)
-    block_reduce_store<2>(acc, a.partials, block_linear);
+}
+
+// which row operations leave partial sums, start from half rows, end in them
+constexpr bool row_has_sums(int op) {
+  return op == ROW_GRAD || op == ROW_GRAD_STEP || op == ROW_HVP || op == ROW_LB_IN || op == ROW_C2R_GRADLIK;
+}
+constexpr bool row_from_half(int op) { return op != ROW_R2C && op != ROW_GRAD_STEP; }
+constexpr bool row_to_half(int op) { return op != ROW_C2R && op != ROW_C2R_DIAG && op != ROW_C2R_GRADLIK; }
+
+template <typename T, int N, int OP, int V = 0>
+__device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>* lds_all, int block_linear) {
+  constexpr int P = Plan<N>::P;
+  constexpr int G = RowShape<N, V>::G;
+  constexpr int LEN = RowShape<N, V>::LEN;
+  constexpr int H = N / 2 + 1;
+  const bool active = (int)threadIdx.x < RowShape<N, V>::THREADS;
+  const int t = threadIdx.x % P;
+  const int ul = active ? (int)threadIdx.x / P : 0;
+  const int u = ublock * G + ul;
+  const bool valid = active && u < a.nunits;
+  const int uc = valid ? u : 0;
+  const long rowA = 2L * uc, rowB = 2L * uc + 1;
+  const BlockRowFft<T, N> fx{t, lds_all + ul * LEN, a.tw, active};
+  double acc[2] = {0.0, 0.0};
+  row_core<T, N, OP>(a, fx, t, active, valid, rowA, rowB, a.in_c + rowA * H, a.out_c + rowA * H, acc);
+  if constexpr (row_has_sums(OP)) block_reduce_store<2>(acc, a.partials, block_linear);
 }
 
 template <typename T, int N, int OP, int V>

@@ -17,6 +17,7 @@
 #define PL_OPS_KERNELS 1
 #include "pl_batch_kernels.hpp"
 #include "pl_passes.hpp"
+#include "pl_plane.hpp"
 #include "pl_linbias_kernels.hpp"
 
 using namespace pl;
@@ -319,14 +320,43 @@ int read_scalars(pl_plan* p) {
   return PL_OK;
 }
 
+// Whether the y and z passes of this grid run as one plane pass.
+template <typename T>
+bool use_plane(const pl_plan* p, int op) {
+  if ((op == ROW_GRAD || op == ROW_GRAD_STEP) && p->model == MODEL_GAUSSIAN) return false;
+  return plane_fits(p->n[1], p->n[2], (int)sizeof(cx<T>));
+}
+
+// The y and z passes of an operator on the half spectrum buf (in place): y
+// inverse for row operations that start from half rows, the row operation,
+// y forward for those that end in half rows; as one plane pass where the
+// grid's planes allow it.  *nb: blocks that left partial sums.
+template <typename T>
+int run_yz(pl_plan* p, int op, cx<T>* buf, RowArgs<T> ra, int* nb = nullptr) {
+  ra.in_c = buf;
+  ra.out_c = buf;
+  int dummy;
+  if (use_plane<T>(p, op)) {
+    ra.ny = p->n[1];
+    ra.nplanes = p->n[0];
+    ra.tw_y = View<T>::tw(p, 1);
+    HIPCHK(p, launch_plane<T>(op, ra, p->stream, nb ? nb : &dummy));
+    return PL_OK;
+  }
+  ColArgs<T> c = col_args<T>(p, 1, buf, buf);
+  c.skip = ra.skip;
+  if (row_from_half(op)) HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, c, nullptr));
+  HIPCHK(p, run_row<T>(p, op, ra, nb));
+  if (row_to_half(op)) HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, c, nullptr));
+  return PL_OK;
+}
+
 // real [N] -> half spectrum out (T precision): z r2c, y fwd, x fwd
 template <typename T>
 int fwd_r2c(pl_plan* p, const T* in, cx<T>* out) {
   RowArgs<T> ra = row_args<T>(p);
   ra.in_r = in;
-  ra.out_c = out;
-  HIPCHK(p, run_row<T>(p, ROW_R2C, ra, nullptr));
-  HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, col_args<T>(p, 1, out, out), nullptr));
+  if (int rc = run_yz<T>(p, ROW_R2C, out, ra)) return rc;
   HIPCHK(p, run_col<T>(p, 0, false, COL_PLAIN, col_args<T>(p, 0, out, out), nullptr));
   return PL_OK;
 }
@@ -335,12 +365,9 @@ int fwd_r2c(pl_plan* p, const T* in, cx<T>* out) {
 template <typename T>
 int inv_c2r(pl_plan* p, const cx<T>* in, cx<T>* tmp, T* out) {
   HIPCHK(p, run_col<T>(p, 0, true, COL_PLAIN, col_args<T>(p, 0, in, tmp), nullptr));
-  HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, col_args<T>(p, 1, tmp, tmp), nullptr));
   RowArgs<T> ra = row_args<T>(p);
-  ra.in_c = tmp;
   ra.out_r = out;
-  HIPCHK(p, run_row<T>(p, ROW_C2R, ra, nullptr));
-  return PL_OK;
+  return run_yz<T>(p, ROW_C2R, tmp, ra);
 }
 
 // q = H p on half spectra; partial sums (p^H q, |q|^2, .) left for a finalize
@@ -350,12 +377,7 @@ int hvp_hat(pl_plan* p, const cx<T>* pin, cx<T>* q, int* nb) {
   Range range("pl hvp");
   cx<T>* t = View<T>::t(p);
   HIPCHK(p, run_col<T>(p, 0, true, COL_PLAIN, col_args<T>(p, 0, pin, t), nullptr));
-  HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, col_args<T>(p, 1, t, t), nullptr));
-  RowArgs<T> ra = row_args<T>(p);
-  ra.in_c = t;
-  ra.out_c = t;
-  HIPCHK(p, run_row<T>(p, ROW_HVP, ra, nullptr));
-  HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, col_args<T>(p, 1, t, t), nullptr));
+  if (int rc = run_yz<T>(p, ROW_HVP, t, row_args<T>(p))) return rc;
   ColArgs<T> ca = col_args<T>(p, 0, t, q);
   ca.base = pin;
   ca.k0_shift = 0.0;
@@ -379,17 +401,13 @@ int grad_hat(pl_plan* p, double* s_out, const double* step_dir = nullptr) {
     ra.scal = p->scal;
   } else {
     HIPCHK(p, run_col<double>(p, 0, true, COL_PLAIN, col_args<double>(p, 0, p->s_hat, t), nullptr));
-    HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
-    ra.in_c = t;
   }
-  ra.out_c = t;
   ra.s_out = s_out;
   ra.e_out = p->e;
   ra.d_out = p->d;
   int nb = 0;
-  HIPCHK(p, run_row<double>(p, step_dir ? ROW_GRAD_STEP : ROW_GRAD, ra, &nb));
+  if (int rc = run_yz<double>(p, step_dir ? ROW_GRAD_STEP : ROW_GRAD, t, ra, &nb)) return rc;
   HIPCHK(p, finalize(p, nb, 2, FIN_STORE, SC_LIK, 1.0));
-  HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   ColArgs<double> ca = col_args<double>(p, 0, t, p->g_hat);
   ca.base = p->s_hat;
   ca.k0_shift = (double)p->N * prior_mean(p);
@@ -492,7 +510,7 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
   // (r, x and the partials of r^H r, r^H M^-1 r).  After each chunk one
   // finalize closes its last iteration for the host's check.
   double* part_c = p->partials + 2 * p->partials_len;
-  int launched = 0, nb5 = 0;
+  int launched = 0, nb5 = 0, rc = PL_OK;
   while (launched < max_cg) {
     const int want = launched == 0 ? (first_chunk > 0 ? first_chunk : check_every)
                                    : next_cg_chunk(p->h_scal, check_every);
@@ -519,23 +537,27 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
         c1.cg_max = (double)max_cg;
       }
       HIPCHK(p, run_col<T>(p, 0, true, first ? COL_CG_INIT : COL_CG_FIRST, c1, &nb1));
-      ColArgs<T> c2 = col_args<T>(p, 1, t, t);
-      c2.skip = skip;
-      HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, c2, nullptr));
       RowArgs<T> ra = row_args<T>(p);
-      ra.in_c = t;
-      ra.out_c = t;
       ra.partials = part_b;
       ra.skip = skip;
-      HIPCHK(p, run_row<T>(p, ROW_HVP, ra, &nb3));
-      // alpha = r^H z / p^H H p, finalized by an extra workgroup of the y
-      // pass that follows (which does not need it; the last x pass does)
-      ColArgs<T> c4 = col_args<T>(p, 1, t, t);
-      c4.skip = skip;
-      c4.fin_on = 1;
-      c4.fin = FinArgs{part_b, nb3, 2, first ? FIN_CG_ALPHA_FIRST : FIN_CG_ALPHA, 0, 1.0, p->scal,
-                       (double)cg_rz_slot(kg), part_a, nb1, invN};
-      HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, c4, nullptr));
+      const int kind_a = first ? FIN_CG_ALPHA_FIRST : FIN_CG_ALPHA;
+      if (use_plane<T>(p, ROW_HVP)) {
+        rc = run_yz<T>(p, ROW_HVP, t, ra, &nb3);
+        if (rc) return rc;
+        HIPCHK(p, finalize(p, nb3, 2, kind_a, 0, 1.0, (double)cg_rz_slot(kg), part_b, part_a, nb1, invN));
+      } else {
+        ColArgs<T> c2 = col_args<T>(p, 1, t, t);
+        c2.skip = skip;
+        HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, c2, nullptr));
+        ra.in_c = t;
+        ra.out_c = t;
+        HIPCHK(p, run_row<T>(p, ROW_HVP, ra, &nb3));
+        // alpha = r^H z / p^H H p, finalized by an extra workgroup of the y
+        // pass that follows (which does not need it; the last x pass does)
+        c2.fin_on = 1;
+        c2.fin = FinArgs{part_b, nb3, 2, kind_a, 0, 1.0, p->scal, (double)cg_rz_slot(kg), part_a, nb1, invN};
+        HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, c2, nullptr));
+      }
       ColArgs<T> c5 = col_args<T>(p, 0, t, t);
       c5.base = pp;
       c5.cg_r = r;
@@ -547,7 +569,7 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
     }
     launched += chunk;
     HIPCHK(p, finalize(p, nb5, 2, FIN_CG_BETA_K, launched, invN, (double)max_cg, part_c));
-    int rc = read_scalars(p);
+    rc = read_scalars(p);
     if (rc) return rc;
     if (p->h_scal[SC_DONE] != 0.0) break;
   }
@@ -1293,21 +1315,19 @@ int pl_grad(pl_plan* p, const double* s, double* grad_out, double* obj_out) {
   cx<double>* t = p->t64;
   RowArgs<double> ra = row_args<double>(p);
   ra.in_r = s;
-  ra.out_c = t;
-  HIPCHK(p, run_row<double>(p, ROW_R2C, ra, nullptr));
-  HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
+  rc = run_yz<double>(p, ROW_R2C, t, ra);
+  if (rc) return rc;
   ColArgs<double> ca = col_args<double>(p, 0, t, t);
   ca.k0_shift = (double)p->N * p->prob.mu;
   int nb = 0;
   HIPCHK(p, run_col<double>(p, 0, false, COL_PRIOR, ca, &nb));
   HIPCHK(p, finalize(p, nb, 1, FIN_STORE, SC_PRIOR, 1.0 / (double)p->N));
-  HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   RowArgs<double> rb = row_args<double>(p);
-  rb.in_c = t;
   rb.out_r = grad_out;
   rb.s_in = s;
   rb.d_out = p->d;
-  HIPCHK(p, run_row<double>(p, ROW_C2R_GRADLIK, rb, &nb));
+  rc = run_yz<double>(p, ROW_C2R_GRADLIK, t, rb, &nb);
+  if (rc) return rc;
   HIPCHK(p, finalize(p, nb, 2, FIN_STORE, SC_LIK, 1.0));
   p->d_valid = true;
   p->d32_valid = false;
@@ -1348,19 +1368,15 @@ int hessvec_real(pl_plan* p, const double* s, const T* v, T* hv) {
   cx<T>* t = View<T>::t(p);
   RowArgs<T> ra = row_args<T>(p);
   ra.in_r = v;
-  ra.out_c = t;
-  HIPCHK(p, run_row<T>(p, ROW_R2C, ra, nullptr));
-  HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, col_args<T>(p, 1, t, t), nullptr));
+  rc = run_yz<T>(p, ROW_R2C, t, ra);
+  if (rc) return rc;
   ColArgs<T> ca = col_args<T>(p, 0, t, t);
   ca.k0_shift = 0.0;
   HIPCHK(p, run_col<T>(p, 0, false, COL_PRIOR, ca, nullptr));
-  HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, col_args<T>(p, 1, t, t), nullptr));
   RowArgs<T> rb = row_args<T>(p);
-  rb.in_c = t;
   rb.out_r = hv;
   rb.v = v;
-  HIPCHK(p, run_row<T>(p, ROW_C2R_DIAG, rb, nullptr));
-  return PL_OK;
+  return run_yz<T>(p, ROW_C2R_DIAG, t, rb);
 }
 
 }  // namespace
@@ -1633,6 +1649,23 @@ extern "C" int pl_compare_fields_noalloc(const int32_t n[3], const double* rec, 
 }
 
 namespace pl {
+// Waves of a plane pass: its larger count of wave-sized groups of transforms
+// (64 / P columns, 64 / P row pairs), spread evenly over at most
+// PLANE_MAX_WAVES.
+int plane_waves(int ny, int nz) {
+  auto per_wave = [](int n) {
+    switch (n) {
+#define PL_C(NN) case NN: return 64 / Plan<NN>::P;
+      PL_PLANE_LENGTHS(PL_C)
+#undef PL_C
+      default: return 64;
+    }
+  };
+  const int cols = (nz / 2 + per_wave(ny)) / per_wave(ny), rows = (ny / 2 + per_wave(nz) - 1) / per_wave(nz);
+  const int groups = std::max(cols, rows), rounds = (groups + PLANE_MAX_WAVES - 1) / PLANE_MAX_WAVES;
+  return (groups + rounds - 1) / rounds;
+}
+
 bool supported_length(int n) {
   switch (n) {
     case 8: case 12: case 16: case 24: case 32: case 48: case 64: case 96: case 128: case 192: case 256: case 512:
@@ -1683,15 +1716,7 @@ int time_cg_step(pl_plan* p, int reps, float* ms) {
     c1.scal = p->scal;
     hipError_t e = run_col<T>(p, 0, true, COL_CG_FIRST, c1, nullptr);
     if (e != hipSuccess) return e;
-    e = run_col<T>(p, 1, true, COL_PLAIN, col_args<T>(p, 1, t, t), nullptr);
-    if (e != hipSuccess) return e;
-    RowArgs<T> ra = row_args<T>(p);
-    ra.in_c = t;
-    ra.out_c = t;
-    e = run_row<T>(p, ROW_HVP, ra, nullptr);
-    if (e != hipSuccess) return e;
-    e = run_col<T>(p, 1, false, COL_PLAIN, col_args<T>(p, 1, t, t), nullptr);
-    if (e != hipSuccess) return e;
+    if (run_yz<T>(p, ROW_HVP, t, row_args<T>(p))) return hipErrorUnknown;
     ColArgs<T> c5 = col_args<T>(p, 0, t, t);
     c5.base = pp;
     c5.cg_r = r;
@@ -1788,8 +1813,10 @@ int tune_precision(pl_plan* p, const std::string& key, std::vector<std::string>&
   }
   // column passes: default, wide, split, extra-wide, wide split and
   // extra-wide split tiles (lengths 128-512); rows: default and wide
-  const int mx = has_wide_variant(p->n[0]) ? 6 : 0, my = has_wide_variant(p->n[1]) ? 6 : 0,
-            mr = has_wide_variant(p->n[2]) ? 1 : 0, mt = p->radial ? 2 : 0;
+  // (no y and z choice where they run as one plane pass)
+  const bool plane = use_plane<T>(p, ROW_HVP);
+  const int mx = has_wide_variant(p->n[0]) ? 6 : 0, my = !plane && has_wide_variant(p->n[1]) ? 6 : 0,
+            mr = !plane && has_wide_variant(p->n[2]) ? 1 : 0, mt = p->radial ? 2 : 0;
   const int reps = p->N >= (1L << 24) ? 5 : 20;
   // the solver's CG step: first the tile variants of the x passes carrying
   // the Krylov updates, y and z and the table those x passes read (default
@@ -3077,20 +3104,15 @@ int lb_conv(pl_plan* p, const double* bk, const double* in, double* out) {
   cx<double>* t = p->t64;
   RowArgs<double> ra = row_args<double>(p);
   ra.in_r = in;
-  ra.out_c = t;
-  HIPCHK(p, run_row<double>(p, ROW_R2C, ra, nullptr));
-  HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
+  if (int rc = run_yz<double>(p, ROW_R2C, t, ra)) return rc;
   ColArgs<double> ca = col_args<double>(p, 0, t, t);
   ca.inv_lam = bk;
   ca.radial = 0;
   ca.k0_shift = 0.0;
   HIPCHK(p, run_col_own_table(p, false, COL_PRIOR, ca, nullptr));
-  HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   RowArgs<double> rb = row_args<double>(p);
-  rb.in_c = t;
   rb.out_r = out;
-  HIPCHK(p, run_row<double>(p, ROW_C2R, rb, nullptr));
-  return PL_OK;
+  return run_yz<double>(p, ROW_C2R, t, rb);
 }
 
 // Linearisation at the real field x: e = phi'(x) (lognormal), rtmp = N / y^2,
@@ -3125,9 +3147,7 @@ int lb_assemble_grad(pl_plan* p, const cx<double>* x_hat, cx<double>* g_out) {
   cx<double>* t = p->t64;
   RowArgs<double> ra = row_args<double>(p);
   ra.in_r = p->s_ws;
-  ra.out_c = t;
-  HIPCHK(p, run_row<double>(p, ROW_R2C, ra, nullptr));
-  HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
+  if (int rc = run_yz<double>(p, ROW_R2C, t, ra)) return rc;
   ColArgs<double> ca = col_args<double>(p, 0, t, g_out);
   ca.base = x_hat;
   ca.k0_shift = (double)p->N * prior_mean(p);
@@ -3177,14 +3197,10 @@ int lb_hvp_hat(pl_plan* p, int model, const double* bk, cx<double>* pin, cx<doub
     // sense, a factor nx: the z pass and the last x pass take 1/nx each.
     const double inv_nx = 1.0 / (double)p->n[0];
     if ((rc = lb_xmul(p, bk))) return rc;
-    HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
     RowArgs<double> ra = row_args<double>(p);
-    ra.in_c = t;
-    ra.out_c = t;
     ra.d = p->rtmp;
     ra.scale *= inv_nx;
-    HIPCHK(p, run_row<double>(p, ROW_HVP, ra, nullptr));
-    HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
+    if ((rc = run_yz<double>(p, ROW_HVP, t, ra))) return rc;
     if ((rc = lb_xmul(p, bk))) return rc;
     ColArgs<double> ca = col_args<double>(p, 0, t, out);
     ca.base = pin;
@@ -3195,39 +3211,27 @@ int lb_hvp_hat(pl_plan* p, int model, const double* bk, cx<double>* pin, cx<doub
   }
   // lognormal: the z passes keep q = F^-1 p (ROW_LB_IN, also forming phi' q)
   // and form phi' g2 + d1 q (ROW_LB_OUT) between their c2r and r2c
-  HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   {
     RowArgs<double> ra = row_args<double>(p);
-    ra.in_c = t;
-    ra.out_c = t;
     ra.out_r = p->preal;
     ra.d = p->e;
     ra.lb_d1 = p->d;
-    HIPCHK(p, run_row<double>(p, ROW_LB_IN, ra, nullptr));
+    if ((rc = run_yz<double>(p, ROW_LB_IN, t, ra))) return rc;
   }
-  HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   if ((rc = lb_xmul(p, bk))) return rc;
-  HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   {
     RowArgs<double> ra = row_args<double>(p);
-    ra.in_c = t;
-    ra.out_c = t;
     ra.d = p->rtmp;
-    HIPCHK(p, run_row<double>(p, ROW_HVP, ra, nullptr));
+    if ((rc = run_yz<double>(p, ROW_HVP, t, ra))) return rc;
   }
-  HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   if ((rc = lb_xmul(p, bk))) return rc;
-  HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   {
     RowArgs<double> ra = row_args<double>(p);
-    ra.in_c = t;
-    ra.out_c = t;
     ra.d = p->e;
     ra.lb_d1 = p->d;
     ra.lb_q = p->preal;
-    HIPCHK(p, run_row<double>(p, ROW_LB_OUT, ra, nullptr));
+    if ((rc = run_yz<double>(p, ROW_LB_OUT, t, ra))) return rc;
   }
-  HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, col_args<double>(p, 1, t, t), nullptr));
   ColArgs<double> ca = col_args<double>(p, 0, t, out);
   ca.base = pin;
   ca.k0_shift = 0.0;
@@ -3339,42 +3343,28 @@ int lb_pcg_fused(pl_plan* p, const double* bk, double tol_abs, int max_cg, int c
       c1.partials = part_a;
       c1.skip = skip;
       HIPCHK(p, run_col<double>(p, 0, true, COL_CG_FIRST, c1, &nb1));
-      ColArgs<double> cy = col_args<double>(p, 1, t, t);
-      cy.skip = skip;
-      HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, cy, nullptr));
       RowArgs<double> r1 = row_args<double>(p);
-      r1.in_c = t;
-      r1.out_c = t;
       r1.out_r = p->preal;
       r1.d = p->e;
       r1.lb_d1 = p->d;
       r1.partials = part_b;
       r1.skip = skip;
-      HIPCHK(p, run_row<double>(p, ROW_LB_IN, r1, &nbq));
-      HIPCHK(p, finalize(p, nbq, 2, FIN_STORE, SC_LB_DQ, 1.0, 0.0, part_b));
-      HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, cy, nullptr));
-      int rc = lb_xmul(p, bk, skip, part_x);
+      int rc = run_yz<double>(p, ROW_LB_IN, t, r1, &nbq);
       if (rc) return rc;
-      HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, cy, nullptr));
+      HIPCHK(p, finalize(p, nbq, 2, FIN_STORE, SC_LB_DQ, 1.0, 0.0, part_b));
+      if ((rc = lb_xmul(p, bk, skip, part_x))) return rc;
       RowArgs<double> r2 = row_args<double>(p);
-      r2.in_c = t;
-      r2.out_c = t;
       r2.d = p->rtmp;
       r2.partials = part_b;
       r2.skip = skip;
-      HIPCHK(p, run_row<double>(p, ROW_HVP, r2, &nbz));
-      HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, cy, nullptr));
+      if ((rc = run_yz<double>(p, ROW_HVP, t, r2, &nbz))) return rc;
       if ((rc = lb_xmul(p, bk, skip, part_x))) return rc;
-      HIPCHK(p, run_col<double>(p, 1, true, COL_PLAIN, cy, nullptr));
       RowArgs<double> r3 = row_args<double>(p);
-      r3.in_c = t;
-      r3.out_c = t;
       r3.d = p->e;
       r3.lb_d1 = p->d;
       r3.lb_q = p->preal;
       r3.skip = skip;
-      HIPCHK(p, run_row<double>(p, ROW_LB_OUT, r3, nullptr));
-      HIPCHK(p, run_col<double>(p, 1, false, COL_PLAIN, cy, nullptr));
+      if ((rc = run_yz<double>(p, ROW_LB_OUT, t, r3))) return rc;
       HIPCHK(p, finalize(p, nbz, 2, FIN_CG_ALPHA_ADD, SC_LB_DQ, 1.0, 0.0, part_b, part_a, nb1, invN));
       ColArgs<double> c5 = col_args<double>(p, 0, t, t);
       c5.base = pp;

@@ -21,4 +21,9 @@ hipError_t launch_col(int N, bool inverse, int op, const ColArgs<T>& a, int nsla
 template <typename T>
 hipError_t launch_row(int N, int op, const RowArgs<T>& a, hipStream_t st, int* nblocks, int variant = 0);
 
+// Plane pass (pl_plane.hpp): op with the y transforms of a.nplanes x planes of
+// a.ny rows of a.n cells, each plane in one workgroup's LDS.
+template <typename T>
+hipError_t launch_plane(int op, const RowArgs<T>& a, hipStream_t st, int* nblocks);
+
 }  // namespace pl
