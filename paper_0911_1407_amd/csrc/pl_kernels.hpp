@@ -153,15 +153,59 @@ enum Scal {
   SC_RZ_ODD = 19,  // r^H M^-1 r after an odd number of CG iterations (cg_rz_slot)
   SC_DF = 20,     // 4 slots
   SC_LS_ALPHA = 24,  // step the device-side Armijo test accepted (-1: none)
+  SC_ALPHA_ODD = 25,  // CG step length taken after an odd number of iterations (cg_alpha_slot)
   SC_ADJ = 26,    // adjoint sums (4 slots)
   SC_LB_DQ = 30,  // linear-bias Krylov step: sum of phi'' B u q^2 (the diagonal part of p^H H p)
-  SC_COUNT = 32
+  SC_TOL_REL2 = 31,  // square of a CG tolerance relative to the first residual (0: SC_TOL2 is given)
+  SC_GAMMA = 32,    // r^H M^-1 r of the running iteration (two-pass CG)
+  SC_COUNT = 40
 };
 
 // The single-plan CG keeps r^H M^-1 r after k completed iterations in
 // slot cg_rz_slot(k): the first pass of iteration k reads slot k - 1 to form
 // beta while one of its workgroups stores slot k.
 __host__ __device__ constexpr int cg_rz_slot(int k) { return (k & 1) ? SC_RZ_ODD : SC_RZ; }
+// Likewise the step length of the iteration after k completed ones: the next
+// iteration reads it while it stores its own.
+__host__ __device__ constexpr int cg_alpha_slot(int k) { return (k & 1) ? SC_ALPHA_ODD : SC_ALPHA; }
+
+// The scalars of one CG iteration in the single-reduction form (Chronopoulos
+// and Gear 1989): with u = M^-1 r, gamma = r^H u and delta = u^H H u,
+//   beta = gamma / gamma_old,  alpha = gamma / (delta - beta gamma / alpha_old)
+// (the denominator is p^H H p of p = u + beta p_old).  Both sums are known
+// before the pass that needs them, so one x pass per iteration does all vector
+// updates.  k: iterations completed; rr = r^H r.  STORE: also the bookkeeping
+// for the next iteration and the host.  Returns whether the solve is over.
+template <bool STORE>
+__device__ __forceinline__ bool cg_scalars(double* scal, double delta, double gamma, double rr, int k, double k_max,
+                                           double tol_rel2, double* alpha, double* beta) {
+  // a tolerance relative to the first residual is known from the first pass on
+  const double tol2 = k == 0 && tol_rel2 > 0.0 ? tol_rel2 * rr : scal[SC_TOL2];
+  double b = 0.0, pq = delta;
+  if (k > 0) {
+    const double g_old = scal[cg_rz_slot(k - 1)], a_old = scal[cg_alpha_slot(k - 1)];
+    b = g_old > 0.0 ? gamma / g_old : 0.0;
+    pq = a_old != 0.0 ? delta - b * gamma / a_old : delta;
+  }
+  const bool end = rr <= tol2 || (double)k >= k_max;
+  const bool bad = !end && !(pq > 0.0);  // breakdown
+  *alpha = end || bad ? 0.0 : gamma / pq;
+  *beta = b;
+  if (STORE) {
+    if (k == 0) {
+      scal[SC_RR0] = rr;
+      scal[SC_TOL2] = tol2;
+    }
+    scal[SC_ITS] = (double)k;
+    scal[SC_RR] = rr;
+    scal[SC_PQ] = pq;
+    scal[SC_BETA] = b;
+    scal[cg_rz_slot(k)] = gamma;
+    scal[cg_alpha_slot(k)] = *alpha;
+    if (end || bad) scal[SC_DONE] = end ? 1.0 : 2.0;
+  }
+  return end || bad;
+}
 
 // Inverse of the preconditioner M_k = 1/lambda_k + dbar (dbar a constant
 // taken from the Hessian diagonal d), in the Krylov vectors' precision:
@@ -178,6 +222,50 @@ __device__ __forceinline__ T precond_inv(T il, double dbar) {
   }
 }
 
+// u = M^-1 r at one mode and its shares of (u^H Lambda^-1 u, r^H u, r^H r):
+// vector arithmetic in the Krylov vectors' precision, sums in FP64.
+template <typename T>
+__device__ __forceinline__ void cg_precondition(cx<T> r, T il, double dbar, double hw, cx<T>& u, double (&acc)[3]) {
+  const T mi = precond_inv<T>(il, dbar);
+  u = {mi * r.x, mi * r.y};
+  const T rr = r.x * r.x + r.y * r.y;
+  acc[0] += hw * (double)(il * (u.x * u.x + u.y * u.y));
+  acc[1] += hw * (double)(mi * rr);
+  acc[2] += hw * (double)rr;
+}
+
+// The step length of one iteration in the textbook order (two x passes per
+// iteration): alpha = gamma / p^H H p with p^H H p = pi + dv (the prior part
+// from the first x pass, the diagonal part from the z or plane pass).  first:
+// the iteration whose first pass was COL_CG_INIT, with gamma and rr from its
+// sums; otherwise gamma is SC_GAMMA.  Returns whether the solve is over.
+template <bool STORE>
+__device__ __forceinline__ bool cg_alpha(double* scal, bool first, double pi, double dv, double gamma, double rr,
+                                         double tol_rel2, double* alpha) {
+  bool end = false;
+  if (first) {
+    const double tol2 = tol_rel2 > 0.0 ? tol_rel2 * rr : scal[SC_TOL2];
+    end = rr <= tol2;  // converged at the start: x stays 0
+    if (STORE) {
+      scal[SC_TOL2] = tol2;
+      scal[SC_RR0] = scal[SC_RR] = rr;
+      scal[cg_rz_slot(0)] = gamma;
+      scal[SC_ITS] = 0.0;
+    }
+  } else {
+    gamma = scal[SC_GAMMA];
+  }
+  const double pq = pi + dv;
+  const bool bad = !end && !(pq > 0.0);  // breakdown
+  *alpha = end || bad ? 0.0 : gamma / pq;
+  if (STORE) {
+    scal[SC_PQ] = pq;
+    scal[SC_ALPHA] = *alpha;
+    if (end || bad) scal[SC_DONE] = end ? 1.0 : 2.0;
+  }
+  return end || bad;
+}
+
 // ---------------------------------------------------------------------------
 // Column pass (x or y axis)
 // ---------------------------------------------------------------------------
@@ -188,8 +276,10 @@ enum ColOp {
   COL_ADDPRIOR = 2,  // forward; out = X + (1/lambda) base (partials K = 3)
   COL_CG_FIRST = 3,  // CG prologue on the input, then inverse transform (partials K = 1)
   COL_CG_LAST = 4,   // forward; q = X + p/lambda; r -= alpha q (partials K = 2)
-  COL_CG_INIT = 5    // COL_CG_FIRST of the first iteration: r0 = sign * rhs, x0 = 0,
-                     // p = M^-1 r0 (partials K = 3)
+  COL_CG_INIT = 5,   // r = sign * rhs; u = M^-1 r, then its inverse transform
+                     // (partials K = 3: u^H Lambda^-1 u, r^H u, r^H r)
+  COL_CG_STEP = 6    // one CG iteration's x pass (forward transform, all vector
+                     // updates, inverse transform of the next u; partials as COL_CG_INIT)
 };
 
 // Arguments of one finalize (finalize_body): sums of per-block partials and
@@ -235,10 +325,7 @@ struct ColArgs {
   const double* scal;  // device scalars (SC_*)
   const double* skip;  // if non-null and *skip != 0 the launch does nothing
   int nt;              // NT_* bits: operands loaded / stored non-temporally
-  // COL_CG_INIT (the first CG iteration's first pass) forms the initial
-  // residual r = cg_rhs_sign * cg_rhs itself (stored to cg_r), x = 0 (stored
-  // to cg_x) and p = M^-1 r, with partials (p^H Lambda^-1 p, r^H M^-1 r,
-  // r^H r).
+  // COL_CG_INIT: the right-hand side, r = cg_rhs_sign * cg_rhs
   const cx<double>* cg_rhs;
   double cg_rhs_sign;
   int variant;  // batched launches: this instance's tile variant (0 or 2)
@@ -254,6 +341,17 @@ struct ColArgs {
   double beta_scale;
   int cg_k;
   double cg_max;
+  // COL_CG_STEP: cg_p = u + beta cg_p and cg_y = F[d v] + beta cg_y
+  // (its share of H p through the diagonal; both unread in the first iteration), cg_r, and on every second iteration
+  // cg_x.  With z_part set (sums of d v^2 left by z_nb blocks of the z or
+  // plane pass; beta_part then holds the previous x pass's sums of three)
+  // every workgroup forms the iteration's scalars itself and workgroup 0
+  // stores them; else they are in scal.
+  cx<T>* cg_p;
+  cx<T>* cg_y;
+  const double* z_part;
+  int z_nb;
+  double tol_rel2;
   // COL_PLAIN launches with fin_on = 1 carry one extra workgroup that runs
   // the finalize `fin` (saving a launch of its own); the host adds it to the
   // grid
@@ -307,6 +405,20 @@ struct ColShape {
 // lengths with a wide variant
 constexpr bool has_wide_variant(int n) { return n == 128 || n == 192 || n == 256 || n == 512; }
 
+// Sums of K interleaved per-block partials by a column pass's workgroup.  (A
+// batched launch may give a tile a larger block than its own.)
+template <typename T, int N, int V, bool BATCHED, int K>
+__device__ __forceinline__ void col_sums(const double* __restrict__ src, int n, double* out) {
+  if constexpr (BATCHED) {
+    if (blockDim.x == 256)
+      fin_sums<256, K>(src, n, out);
+    else
+      fin_sums<128, K>(src, n, out);
+  } else {
+    fin_sums<ColShape<T, N, V>::THREADS, K>(src, n, out);
+  }
+}
+
 // One workgroup's share of a column pass: tile `tile` of slab `slab`.
 // Threads beyond ColShape::THREADS (when a batched launch uses a larger
 // block) only take part in the barriers.
@@ -346,42 +458,42 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
   cx<T>* lds = SPLIT ? reinterpret_cast<cx<T>*>(reinterpret_cast<T*>(lds_all) + cl) : lds_all + cl;
 
   cx<T> v[W];
-  if constexpr (OP == COL_CG_FIRST || OP == COL_CG_INIT) {
+  if constexpr (OP == COL_CG_INIT) {
+    const double dbar = a.scal[SC_DBAR];
+    const double hw = herm_w(col_kz, a.g);
+    double acc[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < W / R0; ++q)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) {
+        const int kx = in_pos<PL, 0>(t, q, r);
+        const long mode = base_off + (long)kx * a.row_stride;
+        cx<T> u = {T(0), T(0)};
+        if (valid) {
+          const T il = inv_lam_at(a.inv_lam, a.radial, a.g, kx, col_ky, col_kz, mode, a.nt & NT_TAB);
+          const cx<double> b = a.cg_rhs[mode];
+          const cx<T> rv = {(T)(a.cg_rhs_sign * b.x), (T)(a.cg_rhs_sign * b.y)};
+          st_stream(a.cg_r + mode, rv, a.nt & NT_R);
+          cg_precondition<T>(rv, il, dbar, hw, u, acc);
+          if (a.cg_p) {  // two-pass CG: p = u, x = 0
+            st_stream(a.cg_p + mode, u, a.nt & NT_P);
+            st_stream(a.cg_x + mode, cx<T>{T(0), T(0)}, a.nt & NT_X);
+          }
+        }
+        v[q * R0 + r] = u;
+      }
+    fft_thread<PL, true, MAP, SPLIT>(v, t, lds, a.tw, active);
+    block_reduce_store<3>(acc, a.partials, block_linear);
+  } else if constexpr (OP == COL_CG_FIRST) {
     // Krylov prologue on the x pass of a half spectrum (columns = (ky, kz)):
     //   p = M^-1 r + beta p_old (in place), partial sum of p^H Lambda^-1 p;
     // then the inverse transform of p.
     const double beta = a.scal[SC_BETA], dbar = a.scal[SC_DBAR];
     const int kz = col_kz;
     const double hw = herm_w(kz, a.g);
-    double acc[3] = {0.0, 0.0, 0.0};
+    double acc[1] = {0.0};
     cx<T>* pio = const_cast<cx<T>*>(a.in);
-    if constexpr (OP == COL_CG_INIT) {
-#pragma unroll
-      for (int q = 0; q < W / R0; ++q)
-#pragma unroll
-        for (int r = 0; r < R0; ++r) {
-          const int e = in_pos<PL, 0>(t, q, r), kx = e, ky = col_ky;
-          long idx = base_off + (long)e * a.row_stride;
-          cx<T> pn = {T(0), T(0)};
-          if (valid) {
-            // r0 = sign * rhs; p = M^-1 r0 (no previous direction)
-            long mode = base_off + (long)e * a.row_stride;
-            const T il = inv_lam_at(a.inv_lam, a.radial, a.g, kx, ky, kz, mode, a.nt & NT_TAB);
-            const T mi = precond_inv<T>(il, dbar);
-            const cx<double> b = a.cg_rhs[idx];
-            const cx<T> rv = {(T)(a.cg_rhs_sign * b.x), (T)(a.cg_rhs_sign * b.y)};
-            st_stream(a.cg_r + idx, rv, a.nt & NT_R);
-            st_stream(a.cg_x + idx, cx<T>{T(0), T(0)}, a.nt & NT_X);  // x0 = 0
-            pn = {mi * rv.x, mi * rv.y};
-            const double rr = (double)rv.x * rv.x + (double)rv.y * rv.y;
-            acc[1] += hw * (double)mi * rr;
-            acc[2] += hw * rr;
-            st_stream(pio + idx, pn, a.nt & NT_P);
-            acc[0] += hw * (double)(il * (pn.x * pn.x + pn.y * pn.y));
-          }
-          v[q * R0 + r] = pn;
-        }
-    } else {
+    {
       double beta_k = beta;
       int cg_k = a.cg_k;
       const double* beta_part = a.beta_part;
@@ -395,15 +507,7 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
       }
       if (beta_part) {
         double v2[2];
-        if constexpr (BATCHED) {
-          // a batched launch may give this tile a larger block than its own
-          if (blockDim.x == 256)
-            fin_sums<256, 2>(beta_part, a.beta_nb, v2);
-          else
-            fin_sums<128, 2>(beta_part, a.beta_nb, v2);
-        } else {
-          fin_sums<ColShape<T, N, V>::THREADS, 2>(beta_part, a.beta_nb, v2);
-        }
+        col_sums<T, N, V, BATCHED, 2>(beta_part, a.beta_nb, v2);
         const double rr = v2[0] * a.beta_scale, rz = v2[1] * a.beta_scale;
         const double rzo = a.scal[cg_rz_slot(cg_k - 1)];
         beta_k = rzo > 0.0 ? rz / rzo : 0.0;
@@ -413,6 +517,7 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
           if constexpr (!BATCHED) sc[SC_ITS] = (double)cg_k;
           sc[SC_RR] = rr;
           sc[cg_rz_slot(cg_k)] = rz;
+          sc[SC_GAMMA] = rz;
           sc[SC_BETA] = beta_k;
           if (done) sc[SC_DONE] = 1.0;
         }
@@ -438,12 +543,7 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
         }
     }
     fft_thread<PL, true, MAP, SPLIT>(v, t, lds, a.tw, active);
-    if constexpr (OP == COL_CG_INIT) {
-      block_reduce_store<3>(acc, a.partials, block_linear);
-    } else {
-      double acc1[1] = {acc[0]};
-      block_reduce_store<1>(acc1, a.partials, block_linear);
-    }
+    block_reduce_store<1>(acc, a.partials, block_linear);
   } else {
 #pragma unroll
   for (int q = 0; q < W / R0; ++q)
@@ -480,11 +580,94 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
     last_to_first<PL, MAP, SPLIT>(v, t, lds, active);
     fft_thread<PL, true, MAP, SPLIT>(v, t, lds, a.tw, active);
     block_reduce_store<1>(acc, a.partials, block_linear);
+  } else if constexpr (OP == COL_CG_STEP) {
+    // forward transform (X = F d v with v = F^-1 u); u = M^-1 r formed again
+    // from r; p = u + beta p, y = X + beta y, so that H p = y + p/lambda (the
+    // prior part is formed from p itself: carried along in the recurrence its
+    // 17 decades cost iterations, 622 instead of 603 at 256^3); r -= alpha H p.
+    // x takes two iterations' steps at once, on every second one, when the
+    // last two directions are both at hand (p_old is read, p is formed), which
+    // saves its read and write on the others.  Then u = M^-1 r of the new
+    // residual, its sums and its inverse transform.
+    int k = a.cg_k;
+    if constexpr (BATCHED) k = (int)a.scal[SC_ITS];
+    double alpha, beta;
+    if (a.z_part) {
+      double dv[2], uv[3];
+      col_sums<T, N, V, BATCHED, 2>(a.z_part, a.z_nb, dv);
+      col_sums<T, N, V, BATCHED, 3>(a.beta_part, a.beta_nb, uv);
+      const double delta = uv[0] * a.beta_scale + dv[0], gamma = uv[1] * a.beta_scale, rr = uv[2] * a.beta_scale;
+      double* sc = const_cast<double*>(a.scal);
+      const bool over = block_linear == 0 && threadIdx.x == 0
+                            ? cg_scalars<true>(sc, delta, gamma, rr, k, a.cg_max, a.tol_rel2, &alpha, &beta)
+                            : cg_scalars<false>(sc, delta, gamma, rr, k, a.cg_max, a.tol_rel2, &alpha, &beta);
+      if (over) return;  // the whole workgroup (every one decides alike)
+    } else {
+      alpha = a.scal[cg_alpha_slot(k)];
+      beta = a.scal[SC_BETA];
+    }
+    const double dbar = a.scal[SC_DBAR], hw = herm_w(col_kz, a.g);
+    const T al = (T)alpha, bt = (T)beta, al_old = k > 0 ? (T)a.scal[cg_alpha_slot(k - 1)] : T(0);
+    fft_thread<PL, false, MAP, SPLIT>(v, t, lds, a.tw, active);
+    double acc[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < W / RL; ++q)
+#pragma unroll
+      for (int m = 0; m < RL; ++m) {
+        const int kx = out_pos<PL, PL::NS - 1>(t, q, m);
+        const long mode = base_off + (long)kx * a.row_stride;
+        cx<T> un = {T(0), T(0)};
+        if (valid) {
+          const T il = inv_lam_at(a.inv_lam, a.radial, a.g, kx, col_ky, col_kz, mode, a.nt & NT_TAB);
+          const cx<T> rv = ld_stream(a.cg_r + mode, a.nt & NT_R);
+          const T mi = precond_inv<T>(il, dbar);
+          cx<T> pn = {mi * rv.x, mi * rv.y}, po = {T(0), T(0)}, yn = v[q * RL + m];
+          if (k > 0) {
+            po = ld_stream(a.cg_p + mode, a.nt & NT_P);
+            const cx<T> yo = ld_stream(a.cg_y + mode, a.nt & NT_P);
+            pn = {pn.x + bt * po.x, pn.y + bt * po.y};
+            yn = {yn.x + bt * yo.x, yn.y + bt * yo.y};
+          }
+          const cx<T> rn = {rv.x - al * (yn.x + il * pn.x), rv.y - al * (yn.y + il * pn.y)};
+          st_stream(a.cg_p + mode, pn, a.nt & NT_P);
+          st_stream(a.cg_y + mode, yn, a.nt & NT_P);
+          st_stream(a.cg_r + mode, rn, a.nt & NT_R);
+          if (k & 1) {
+            cx<T> xn = {al_old * po.x + al * pn.x, al_old * po.y + al * pn.y};
+            if (k > 1) xn = xn + ld_stream(a.cg_x + mode, a.nt & NT_X);
+            st_stream(a.cg_x + mode, xn, a.nt & NT_X);
+          }
+          cg_precondition<T>(rn, il, dbar, hw, un, acc);
+        }
+        v[q * RL + m] = un;
+      }
+    last_to_first<PL, MAP, SPLIT>(v, t, lds, active);
+    fft_thread<PL, true, MAP, SPLIT>(v, t, lds, a.tw, active);
+    block_reduce_store<3>(acc, a.partials, block_linear);
   } else if constexpr (OP == COL_CG_LAST) {
     // forward transform; q = X + p/lambda (= H p); r -= alpha q and
     // x += alpha p in place; partials (r^H r, r^H M^-1 r).  q is not stored.
     // p and 1/lambda at the output positions are loaded before the
-    // transform so that their latency overlaps it.
+    // transform so that their latency overlaps it.  With z_part set every
+    // workgroup forms alpha itself and workgroup 0 stores it.
+    double alpha = 0.0;
+    if (a.z_part) {
+      const bool first = !BATCHED && a.cg_k == 0;
+      double dv[2], e[3] = {0.0, 0.0, 0.0};
+      col_sums<T, N, V, BATCHED, 2>(a.z_part, a.z_nb, dv);
+      if (first)
+        col_sums<T, N, V, BATCHED, 3>(a.beta_part, a.beta_nb, e);
+      else
+        col_sums<T, N, V, BATCHED, 1>(a.beta_part, a.beta_nb, e);
+      double* sc = const_cast<double*>(a.scal);
+      const double pi = e[0] * a.beta_scale, gamma = e[1] * a.beta_scale, rr = e[2] * a.beta_scale;
+      const bool over = block_linear == 0 && threadIdx.x == 0
+                            ? cg_alpha<true>(sc, first, pi, dv[0], gamma, rr, a.tol_rel2, &alpha)
+                            : cg_alpha<false>(sc, first, pi, dv[0], gamma, rr, a.tol_rel2, &alpha);
+      if (over) return;  // the whole workgroup (every one decides alike)
+    } else {
+      alpha = a.scal[SC_ALPHA];
+    }
     const int kz = col_kz;
     cx<T> pre_p[PRELOAD ? W : 1];
     T pre_il[PRELOAD ? W : 1];
@@ -501,7 +684,7 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
     }
     fft_thread<PL, false, MAP, SPLIT>(v, t, lds, a.tw, active);
     const double hw = herm_w(kz, a.g);
-    const double alpha = a.scal[SC_ALPHA], dbar = a.scal[SC_DBAR];
+    const double dbar = a.scal[SC_DBAR];
     double acc[2] = {0.0, 0.0};
 #pragma unroll
     for (int q = 0; q < W / RL; ++q)
@@ -1142,7 +1325,8 @@ __global__ void __launch_bounds__(RED_THREADS) cg_init_kernel(const cx<double>* 
 }
 
 enum FinKind { FIN_STORE = 0, FIN_CG_INIT = 1, FIN_CG_ALPHA = 2, FIN_CG_BETA = 3, FIN_DBAR = 4, FIN_CG_ALPHA_ADD = 5,
-               FIN_CG_ALPHA_FIRST = 6, FIN_CG_BETA_K = 7, FIN_CG_BETA_DEV = 8 };
+               FIN_CG_STEP = 6, FIN_CG_CHECK = 7, FIN_CG_BETA_DEV = 8, FIN_CG_ALPHA_FIRST = 9,
+               FIN_CG_ALPHA_K = 10, FIN_CG_BETA_K = 11 };
 
 // Sum partials[nb][K] in a fixed order; then scalar bookkeeping.
 // kind FIN_CG_ALPHA: p^H H p = scale2 * sum(partials2[nb2]) (prior part from
@@ -1204,7 +1388,7 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
   double extra = 0.0;
   double e3[3] = {0.0, 0.0, 0.0};
   if (partials2) {
-    if (kind == FIN_CG_ALPHA_FIRST) {
+    if (kind == FIN_CG_STEP || kind == FIN_CG_ALPHA_FIRST) {
       fin_sums<NT, 3>(partials2, nb2, e3);
     } else {
       fin_sums<NT, 1>(partials2, nb2, e3);
@@ -1222,6 +1406,7 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       scal[SC_RR] = v[0];
       const double rzo = scal[cg_rz_slot(k - 1)];
       scal[cg_rz_slot(k)] = v[1];
+      scal[SC_GAMMA] = v[1];
       scal[SC_BETA] = rzo > 0.0 ? v[1] / rzo : 0.0;
       if (v[0] <= scal[SC_TOL2] || (double)k >= aux) scal[SC_DONE] = 1.0;
       return;
@@ -1233,6 +1418,7 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       break;
     case FIN_CG_INIT:
       scal[SC_RZ] = v[0];
+      scal[SC_GAMMA] = v[0];
       scal[SC_RR] = v[1];
       scal[SC_RR0] = v[1];
       scal[SC_DONE] = (v[1] <= scal[SC_TOL2]) ? 1.0 : 0.0;
@@ -1256,26 +1442,33 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       scal[SC_ALPHA] = al;
       break;
     }
-    case FIN_CG_ALPHA_FIRST: {
-      // first iteration, whose first pass also formed r0 = sign * rhs:
-      // partials2 = (p^H Lambda^-1 p, r^H M^-1 r, r^H r) of that pass
-      const double rz = e3[1] * scale2, rr = e3[2] * scale2;
-      scal[SC_RZ] = rz;
-      scal[SC_RR] = rr;
-      scal[SC_RR0] = rr;
-      scal[SC_ITS] = 0.0;
-      scal[SC_BETA] = 0.0;
-      scal[SC_ALPHA] = 0.0;
-      if (rr <= scal[SC_TOL2]) {
-        scal[SC_DONE] = 1.0;  // converged at the start: x stays 0
-        break;
-      }
-      const double pq = v[0] + extra;
-      scal[SC_PQ] = pq;
-      if (pq > 0.0)
-        scal[SC_ALPHA] = rz / pq;
-      else
-        scal[SC_DONE] = 2.0;  // breakdown
+    case FIN_CG_STEP: {
+      // the scalars of iteration dst + 1, from the z pass's sum of d v^2 and
+      // the last x pass's (u^H Lambda^-1 u, r^H u, r^H r); aux: the iteration
+      // cap, scal[SC_TOL_REL2] the relative tolerance
+      if (scal[SC_DONE] != 0.0) break;  // iteration skipped
+      double alpha, beta;
+      cg_scalars<true>(scal, e3[0] * scale2 + v[0], e3[1] * scale2, e3[2] * scale2, dst, aux, scal[SC_TOL_REL2], &alpha,
+                       &beta);
+      break;
+    }
+    case FIN_CG_ALPHA_FIRST:
+    case FIN_CG_ALPHA_K: {
+      // the step length of the two-pass CG (cg_alpha), of its first iteration
+      // and of the later ones
+      if (scal[SC_DONE] != 0.0) break;  // iteration skipped
+      double alpha;
+      cg_alpha<true>(scal, kind == FIN_CG_ALPHA_FIRST, e3[0] * scale2, v[0], e3[1] * scale2, e3[2] * scale2,
+                     scal[SC_TOL_REL2], &alpha);
+      break;
+    }
+    case FIN_CG_BETA_K: {
+      // the bookkeeping a COL_CG_FIRST pass with beta_part does, for the
+      // host's check after a chunk: dst = iterations completed
+      if (scal[SC_DONE] != 0.0) break;  // iteration skipped
+      scal[SC_ITS] = (double)dst;
+      scal[SC_RR] = v[0];
+      if (v[0] <= scal[SC_TOL2] || (double)dst >= aux) scal[SC_DONE] = 1.0;
       break;
     }
     case FIN_CG_BETA: {
@@ -1288,16 +1481,13 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       if (v[0] <= scal[SC_TOL2] || scal[SC_ITS] >= aux) scal[SC_DONE] = 1.0;
       break;
     }
-    case FIN_CG_BETA_K: {
-      // the bookkeeping a COL_CG_FIRST pass with beta_part does, for the
-      // host's check after a chunk: dst = iterations completed
+    case FIN_CG_CHECK: {
+      // the convergence test a COL_CG_STEP pass starts with, for the host's
+      // check after a chunk: dst = iterations completed
       if (scal[SC_DONE] != 0.0) break;  // iteration skipped
       scal[SC_ITS] = (double)dst;
-      scal[SC_RR] = v[0];
-      const double rzo = scal[cg_rz_slot(dst - 1)];
-      scal[cg_rz_slot(dst)] = v[1];
-      scal[SC_BETA] = rzo > 0.0 ? v[1] / rzo : 0.0;
-      if (v[0] <= scal[SC_TOL2] || (double)dst >= aux) scal[SC_DONE] = 1.0;
+      scal[SC_RR] = v[2];
+      if (v[2] <= scal[SC_TOL2] || (double)dst >= aux) scal[SC_DONE] = 1.0;
       break;
     }
     case FIN_DBAR:
@@ -1476,11 +1666,12 @@ __global__ void set_scalar_kernel(double* scal, int idx, double value) {
   if (threadIdx.x == 0 && blockIdx.x == 0) scal[idx] = value;
 }
 
-// Start of a CG solve whose first iteration forms the initial residual
-// itself (COL_CG_INIT): stopping threshold, iteration count and state.
-__global__ void cg_start_kernel(double* scal, double tol2) {
+// Start of a CG solve: stopping threshold (absolute, or relative to the first
+// residual), iteration count and state.
+__global__ void cg_start_kernel(double* scal, double tol2, double tol_rel2) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     scal[SC_TOL2] = tol2;
+    scal[SC_TOL_REL2] = tol_rel2;
     scal[SC_DONE] = 0.0;
     scal[SC_ITS] = 0.0;
     scal[SC_BETA] = 0.0;
@@ -1517,6 +1708,25 @@ __global__ void __launch_bounds__(RED_THREADS) axpy_hat_dev_kernel(cx<double>* _
 }
 
 #ifdef PL_OPS_KERNELS
+// The part of the CG's x that COL_CG_STEP has not added yet: after an odd
+// number of iterations the last direction's step, after none x = 0.
+__global__ void __launch_bounds__(RED_THREADS) cg_flush_kernel(cx<double>* __restrict__ x,
+                                                               const cx<double>* __restrict__ p,
+                                                               const double* __restrict__ scal, long nh) {
+  const int its = (int)scal[SC_ITS];
+  if (its > 0 && !(its & 1)) return;
+  const double al = its > 0 ? scal[cg_alpha_slot(its - 1)] : 0.0;
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nh; i += (long)gridDim.x * blockDim.x) {
+    cx<double> xn = {0.0, 0.0};
+    if (its > 0) {
+      const cx<double> pv = p[i];
+      xn = {al * pv.x, al * pv.y};
+      if (its > 1) xn = xn + x[i];
+    }
+    x[i] = xn;
+  }
+}
+
 // Armijo test of the first batch of trial steps a0, a0/2, a0/4, a0/8 on the
 // device: decrease a b + a^2 c / 2 + sum_i [...] (slots SC_LS_B, SC_LS_C,
 // SC_DF + j) against c1 a slope; the first accepted step goes to

@@ -74,7 +74,8 @@ struct pl_plan {
   size_t ws_bytes = 0;
   char* ws = nullptr;
   // spectral FP64 vectors
-  cx<double>*s_hat = nullptr, *g_hat = nullptr, *x64 = nullptr, *r64 = nullptr, *p64 = nullptr, *t64 = nullptr;
+  cx<double>*s_hat = nullptr, *g_hat = nullptr, *x64 = nullptr, *r64 = nullptr, *p64 = nullptr, *t64 = nullptr,
+      *y64 = nullptr;
   // spectral FP32 vectors (mixed precision)
   cx<float>*x32 = nullptr, *r32 = nullptr, *p32 = nullptr, *t32 = nullptr;
   // real fields
@@ -146,6 +147,7 @@ size_t carve(pl_plan* p, char* base) {
   p->r64 = (cx<double>*)take(c64);
   p->p64 = (cx<double>*)take(c64);
   p->t64 = (cx<double>*)take(c64);
+  p->y64 = (cx<double>*)take(c64);
   p->s_ws = (double*)take(r64);
   p->e = (double*)take(r64);
   p->d = (double*)take(r64);
@@ -265,7 +267,7 @@ template <typename T>
 hipError_t run_col(pl_plan* p, int axis, bool inverse, int op, const ColArgs<T>& a, int* nb) {
   int dummy;
   const int pi = sizeof(T) == 4 ? 1 : 0;
-  const bool krylov = op == COL_CG_FIRST || op == COL_CG_LAST || op == COL_CG_INIT;
+  const bool krylov = op == COL_CG_FIRST || op == COL_CG_LAST || op == COL_CG_INIT || op == COL_CG_STEP;
   const int v = axis == 1 ? p->var[pi][V_Y] : p->var[pi][krylov ? V_XCG : V_XOP];
   const int nslabs = axis == 0 ? 1 : p->n[0];
   if (op == COL_PLAIN) return launch_col<T>(p->n[axis], inverse, op, a, nslabs, p->stream, nb ? nb : &dummy, v);
@@ -440,18 +442,30 @@ int ensure_d32(pl_plan* p) {
 }
 
 // ---------------------------------------------------------------------------
-// Preconditioned CG on H x = sign * rhs (spectral, T-precision vectors), with
-// the vector updates fused into the Hessian-vector passes:
-//   pass 1 (x, inverse):  p = M^-1 r + beta p; partial p^H Lambda^-1 p
-//   passes 2-4:           y inverse, z (c2r, times d, r2c; partial sum d v^2), y forward
-//   finalize:             alpha = r^H M^-1 r / (p^H Lambda^-1 p + sum d v^2)
-//   pass 5 (x, forward):  r -= alpha (F[d v] + p/lambda); x += alpha p;
-//                         partials r^H r, r^H M^-1 r
-//   finalize:             beta, convergence
-// alpha = -(xi^T grad Q)/(xi^T H xi) is the step of eq. (New5) for the
-// local quadratic model; it is known before the last pass, which applies it
-// to r and x without storing H p.  Iterations queued after convergence exit
-// at once on the device (the passes read the done flag).
+// Preconditioned CG on H x = sign * rhs (spectral, T-precision vectors) with
+// the vector updates fused into the Hessian product's x passes.  The z part --
+// y inverse, z (c2r, times d, r2c; sum d v^2), y forward -- is one plane pass
+// where the planes fit.
+// FP64 vectors, one x pass per iteration (single-reduction form, cg_scalars):
+//   start (x):    r = sign * rhs, u = M^-1 r, sums, x inverse of u
+//   z part:       on u
+//   x pass:       x forward, p = u + beta p, y = F[d v] + beta y (y: the
+//                 diagonal part of H p, so H p = y + p/lambda), x += alpha p,
+//                 r -= alpha H p, u = M^-1 r, sums, x inverse of u
+// FP32 vectors, two x passes (the textbook order):
+//   first x pass: p = M^-1 r + beta p, x inverse; partial p^H Lambda^-1 p
+//   z part:       on p
+//   last x pass:  x forward, r -= alpha (F[d v] + p/lambda), x += alpha p; sums
+// The single pass saves a launch, a table and, adding x's two last steps at
+// once, one of 16 half-spectrum transfers (256^3 FP64: 436 -> 414 us per
+// iteration; 96^3 adjoint solve 12.1 -> 9.9 ms; same iteration counts).  In
+// FP32 the recurrence for y loses what the textbook order recomputes: a 128^3
+// solve took 798 iterations instead of 476.
+// alpha = -(xi^T grad Q)/(xi^T H xi) is the step of eq. (New5) for the local
+// quadratic model (xi = p).  The scalars are formed by every workgroup of the x
+// pass that needs them after a plane pass (at most about 260 + 256 partial sums),
+// by an extra workgroup of the y forward pass otherwise.  Iterations queued
+// after convergence exit at once on the device (the passes read the done flag).
 // *its receives iterations that changed x, *hvps the Hessian products run.
 // ---------------------------------------------------------------------------
 // CG iterations to queue after a host check found the solve still running:
@@ -470,117 +484,122 @@ int next_cg_chunk(const double* sc, int check_every) {
   return std::max(4, std::min(want, (int)its));
 }
 
-// With tol_rel_of_rhs == 0 (an absolute tolerance known in advance) the
-// first iteration's first pass forms the initial residual itself
-// (COL_CG_INIT), so no separate initialisation pass runs;
-// with a tolerance relative to ||rhs|| an initialisation pass and one
-// read-back of ||rhs|| come first.  first_chunk (> 0) sets how many
-// iterations are queued before the first host check; later chunks are
-// sized from the residual decrease so far (next_cg_chunk).
+// tol_rel_of_rhs > 0: the tolerance is relative to ||rhs||, which the start
+// pass's sums give on the device.  first_chunk (> 0) sets how many iterations
+// are queued before the first host check; later chunks are sized from the
+// residual decrease so far (next_cg_chunk).
 template <typename T>
 int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double tol_rel_of_rhs, int max_cg,
         int check_every, int* its, int* hvps, double* rel_res, double* rhs_norm, int first_chunk = 0) {
+  constexpr bool kOnePass = sizeof(T) == 8;
   cx<T>*x = View<T>::x(p), *r = View<T>::r(p), *pp = View<T>::pv(p), *t = View<T>::t(p);
-  const T* tab = View<T>::tab(p);
   const double invN = 1.0 / (double)p->N;
-  double* part_a = p->partials;
-  double* part_b = p->partials + p->partials_len;
-  const bool fused = !(tol_rel_of_rhs > 0.0);
-  double rr0 = 0.0;
-  if (fused) {
-    hipLaunchKernelGGL(cg_start_kernel, dim3(1), dim3(64), 0, p->stream, p->scal, tol_abs * tol_abs);
-    HIPCHK(p, hipGetLastError());
-  } else {
-    HIPCHK(p, set_scalar(p, SC_TOL2, tol_abs * tol_abs));
-    hipLaunchKernelGGL((cg_init_kernel<T>), dim3(NB_RED), dim3(RED_THREADS), 0, p->stream, rhs, sign, x, r, pp, tab,
-                       TAB_MODE, p->g, p->Nh, p->scal, p->partials);
-    HIPCHK(p, hipGetLastError());
-    HIPCHK(p, finalize(p, NB_RED, 2, FIN_CG_INIT, 0, invN));
-    int rc = read_scalars(p);
-    if (rc) return rc;
-    rr0 = p->h_scal[SC_RR];
-    double tol2 = tol_rel_of_rhs * tol_rel_of_rhs * rr0;
-    HIPCHK(p, set_scalar(p, SC_TOL2, tol2));
-    HIPCHK(p, set_scalar(p, SC_DONE, rr0 <= tol2 ? 1.0 : 0.0));
+  const double* skip = p->scal + SC_DONE;
+  // regions: the x passes' sums (in turn: one is read while the next is
+  // written) and the z part's
+  double* part_x[2] = {p->partials, p->partials + 2 * p->partials_len};
+  double* part_z = p->partials + p->partials_len;
+  const double tol_rel2 = tol_rel_of_rhs > 0.0 ? tol_rel_of_rhs * tol_rel_of_rhs : 0.0;
+  hipLaunchKernelGGL(cg_start_kernel, dim3(1), dim3(64), 0, p->stream, p->scal, tol_abs * tol_abs, tol_rel2);
+  HIPCHK(p, hipGetLastError());
+  const bool plane = use_plane<T>(p, ROW_HVP);
+  ColArgs<T> cx0 = col_args<T>(p, 0, t, t);  // what the x passes share
+  cx0.cg_r = r;
+  cx0.cg_x = x;
+  cx0.scal = p->scal;
+  cx0.cg_max = (double)max_cg;
+  cx0.tol_rel2 = tol_rel2;
+  cx0.beta_scale = invN;
+  int nbx = 0, nbz = 0, rc = PL_OK;
+  {
+    ColArgs<T> c = cx0;
+    c.partials = part_x[0];
+    c.cg_rhs = rhs;
+    c.cg_rhs_sign = sign;
+    c.cg_p = kOnePass ? nullptr : pp;
+    HIPCHK(p, run_col<T>(p, 0, true, COL_CG_INIT, c, &nbx));
   }
-  // Per iteration k: the first x pass (p = M^-1 r + beta p, which from k = 1
-  // on also closes iteration k - 1: beta, the convergence test and the
-  // bookkeeping, from the last pass's partials in part_c), y, z (with
-  // p^H H p), y (whose extra workgroup finalizes alpha), the last x pass
-  // (r, x and the partials of r^H r, r^H M^-1 r).  After each chunk one
-  // finalize closes its last iteration for the host's check.
-  double* part_c = p->partials + 2 * p->partials_len;
-  int launched = 0, nb5 = 0, rc = PL_OK;
+  int launched = 0;
   while (launched < max_cg) {
     const int want = launched == 0 ? (first_chunk > 0 ? first_chunk : check_every)
                                    : next_cg_chunk(p->h_scal, check_every);
-    int chunk = std::min(want, max_cg - launched);
+    const int chunk = std::min(want, max_cg - launched);
     Range range("pl cg chunk");
-    for (int k = 0; k < chunk; ++k) {
-      const int kg = launched + k;  // iterations before this one
-      int nb1 = 0, nb3 = 0;
-      const bool first = fused && kg == 0;
-      const double* skip = p->scal + SC_DONE;
-      ColArgs<T> c1 = col_args<T>(p, 0, pp, t);
-      c1.cg_r = r;
-      c1.scal = p->scal;
-      c1.partials = part_a;
-      c1.skip = skip;
-      c1.cg_rhs = rhs;
-      c1.cg_rhs_sign = sign;
-      c1.cg_x = x;
-      if (kg > 0) {
-        c1.beta_part = part_c;
-        c1.beta_nb = nb5;
-        c1.beta_scale = invN;
-        c1.cg_k = kg;
-        c1.cg_max = (double)max_cg;
+    for (int i = 0; i < chunk; ++i) {
+      const int k = launched + i;  // iterations before this one
+      // the x pass's sums that the scalars of this iteration come from
+      double* part_in = kOnePass ? part_x[k & 1] : part_x[0];
+      if (!kOnePass && k > 0) {
+        ColArgs<T> c = cx0;
+        c.in = pp;
+        c.beta_part = part_x[1];
+        c.beta_nb = nbx;
+        c.cg_k = k;
+        c.partials = part_x[0];
+        c.skip = skip;
+        HIPCHK(p, run_col<T>(p, 0, true, COL_CG_FIRST, c, &nbx));
       }
-      HIPCHK(p, run_col<T>(p, 0, true, first ? COL_CG_INIT : COL_CG_FIRST, c1, &nb1));
       RowArgs<T> ra = row_args<T>(p);
-      ra.partials = part_b;
+      ra.partials = part_z;
       ra.skip = skip;
-      const int kind_a = first ? FIN_CG_ALPHA_FIRST : FIN_CG_ALPHA;
-      if (use_plane<T>(p, ROW_HVP)) {
-        rc = run_yz<T>(p, ROW_HVP, t, ra, &nb3);
+      ColArgs<T> c = cx0;
+      c.skip = skip;
+      c.cg_k = k;
+      if (plane) {
+        rc = run_yz<T>(p, ROW_HVP, t, ra, &nbz);
         if (rc) return rc;
-        HIPCHK(p, finalize(p, nb3, 2, kind_a, 0, 1.0, (double)cg_rz_slot(kg), part_b, part_a, nb1, invN));
+        c.z_part = part_z;
+        c.z_nb = nbz;
+        c.beta_part = part_in;
+        c.beta_nb = nbx;
       } else {
-        ColArgs<T> c2 = col_args<T>(p, 1, t, t);
-        c2.skip = skip;
-        HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, c2, nullptr));
+        ColArgs<T> cy = col_args<T>(p, 1, t, t);
+        cy.skip = skip;
+        HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, cy, nullptr));
         ra.in_c = t;
         ra.out_c = t;
-        HIPCHK(p, run_row<T>(p, ROW_HVP, ra, &nb3));
-        // alpha = r^H z / p^H H p, finalized by an extra workgroup of the y
-        // pass that follows (which does not need it; the last x pass does)
-        c2.fin_on = 1;
-        c2.fin = FinArgs{part_b, nb3, 2, kind_a, 0, 1.0, p->scal, (double)cg_rz_slot(kg), part_a, nb1, invN};
-        HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, c2, nullptr));
+        HIPCHK(p, run_row<T>(p, ROW_HVP, ra, &nbz));
+        // the iteration's scalars, by an extra workgroup of the y pass
+        // (which does not need them; the x pass does)
+        const int kind = kOnePass ? FIN_CG_STEP : (k == 0 ? FIN_CG_ALPHA_FIRST : FIN_CG_ALPHA_K);
+        cy.fin_on = 1;
+        cy.fin = FinArgs{part_z, nbz, 2, kind, k, 1.0, p->scal, (double)max_cg, part_in, nbx, invN};
+        HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, cy, nullptr));
       }
-      ColArgs<T> c5 = col_args<T>(p, 0, t, t);
-      c5.base = pp;
-      c5.cg_r = r;
-      c5.cg_x = x;
-      c5.scal = p->scal;
-      c5.partials = part_c;
-      c5.skip = skip;
-      HIPCHK(p, run_col<T>(p, 0, false, COL_CG_LAST, c5, &nb5));
+      if constexpr (kOnePass) {
+        c.cg_p = pp;
+        c.cg_y = p->y64;
+        c.partials = part_x[(k + 1) & 1];
+        HIPCHK(p, run_col<T>(p, 0, false, COL_CG_STEP, c, &nbx));
+      } else {
+        c.base = pp;
+        c.partials = part_x[1];
+        HIPCHK(p, run_col<T>(p, 0, false, COL_CG_LAST, c, &nbx));
+      }
     }
     launched += chunk;
-    HIPCHK(p, finalize(p, nb5, 2, FIN_CG_BETA_K, launched, invN, (double)max_cg, part_c));
+    if (kOnePass)
+      HIPCHK(p, finalize(p, nbx, 3, FIN_CG_CHECK, launched, invN, (double)max_cg, part_x[launched & 1]));
+    else
+      HIPCHK(p, finalize(p, nbx, 2, FIN_CG_BETA_K, launched, invN, (double)max_cg, part_x[1]));
     rc = read_scalars(p);
     if (rc) return rc;
     if (p->h_scal[SC_DONE] != 0.0) break;
   }
   *its = (int)p->h_scal[SC_ITS];
+  if constexpr (kOnePass) {
+    if (*its == 0 || (*its & 1)) {
+      hipLaunchKernelGGL(cg_flush_kernel, dim3(NB_RED), dim3(RED_THREADS), 0, p->stream, x, pp, p->scal, p->Nh);
+      HIPCHK(p, hipGetLastError());
+    }
+  }
   // Hessian products that ran: one per counted iteration, plus the partial
-  // one of a breakdown (or of a fused first iteration whose residual was
-  // already below the tolerance); queued iterations after convergence exit
+  // one of a breakdown (or of a first iteration whose residual was already
+  // below an absolute tolerance); queued iterations after convergence exit
   // at once
-  *hvps = *its + ((p->h_scal[SC_DONE] == 2.0 || (fused && *its == 0)) ? 1 : 0);
+  *hvps = *its + ((p->h_scal[SC_DONE] == 2.0 || (!(tol_rel2 > 0.0) && *its == 0)) ? 1 : 0);
   if (rel_res) *rel_res = std::sqrt(std::max(0.0, p->h_scal[SC_RR]));
-  if (rhs_norm) *rhs_norm = std::sqrt(rr0);
+  if (rhs_norm) *rhs_norm = std::sqrt(p->h_scal[SC_RR0]);
   return PL_OK;
 }
 
@@ -1691,9 +1710,8 @@ std::string arch_name() {
   return c == std::string::npos ? a : a.substr(0, c);
 }
 
-// Time one fused CG step (the solver's hot loop: pass 1 with the Krylov
-// prologue, y inverse, z, y forward, pass 5 with the Krylov updates), average
-// of `reps`, with the plan's current variants.  Runs on zeroed vectors with
+// Time one fused CG step (the solver's hot loop: the z part and the x passes
+// with the Krylov updates), average of `reps`, with the plan's current variants.  Runs on zeroed vectors with
 // zero step lengths, so nothing is left in a meaningful state.
 template <typename T>
 int fill_hash(pl_plan* p, T* x, long n, unsigned seed, double lo = -1.0, double span = 2.0) {
@@ -1710,19 +1728,28 @@ int time_cg_step(pl_plan* p, int reps, float* ms) {
   if (int frc = fill_hash<T>(p, (T*)r, 2 * p->Nh, 2)) return frc;
   if (int frc = fill_hash<T>(p, (T*)pp, 2 * p->Nh, 3)) return frc;
   HIPCHK(p, hipMemsetAsync(p->scal, 0, sizeof(double) * SC_COUNT, p->stream));  // alpha = beta = 0
+  int count = 0;
   auto step = [&]() -> hipError_t {
-    ColArgs<T> c1 = col_args<T>(p, 0, pp, t);
-    c1.cg_r = r;
-    c1.scal = p->scal;
-    hipError_t e = run_col<T>(p, 0, true, COL_CG_FIRST, c1, nullptr);
-    if (e != hipSuccess) return e;
-    if (run_yz<T>(p, ROW_HVP, t, row_args<T>(p))) return hipErrorUnknown;
     ColArgs<T> c5 = col_args<T>(p, 0, t, t);
     c5.base = pp;
     c5.cg_r = r;
     c5.cg_x = x;
     c5.scal = p->scal;
-    return run_col<T>(p, 0, false, COL_CG_LAST, c5, nullptr);
+    if constexpr (sizeof(T) == 4) {
+      ColArgs<T> c1 = c5;
+      c1.in = pp;
+      if (hipError_t e = run_col<T>(p, 0, true, COL_CG_FIRST, c1, nullptr)) return e;
+    }
+    if (run_yz<T>(p, ROW_HVP, t, row_args<T>(p))) return hipErrorUnknown;
+    if constexpr (sizeof(T) == 8) {
+      ColArgs<T> c = c5;
+      c.cg_p = pp;
+      c.cg_y = p->y64;
+      c.cg_k = 2 + (count++ & 1);  // x is updated on every second iteration
+      return run_col<T>(p, 0, false, COL_CG_STEP, c, nullptr);
+    } else {
+      return run_col<T>(p, 0, false, COL_CG_LAST, c5, nullptr);
+    }
   };
   hipEvent_t e0, e1;
   HIPCHK(p, hipEventCreate(&e0));

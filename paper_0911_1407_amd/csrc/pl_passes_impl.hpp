@@ -30,6 +30,10 @@ static hipError_t col_launch_n(bool inverse, int op, const ColArgs<T>& a, int ns
     hipLaunchKernelGGL((col_kernel<T, N, true, COL_CG_FIRST, V>), grid, dim3(S::THREADS), 0, st, a);
   } else if (op == COL_CG_INIT) {
     hipLaunchKernelGGL((col_kernel<T, N, true, COL_CG_INIT, V>), grid, dim3(S::THREADS), 0, st, a);
+#if PL_T_IS_DOUBLE
+  } else if (op == COL_CG_STEP) {
+    hipLaunchKernelGGL((col_kernel<T, N, false, COL_CG_STEP, V>), grid, dim3(S::THREADS), 0, st, a);
+#endif
   } else if (op == COL_CG_LAST) {
     hipLaunchKernelGGL((col_kernel<T, N, false, COL_CG_LAST, V>), grid, dim3(S::THREADS), 0, st, a);
   } else {
