@@ -23,19 +23,16 @@ inline bool batch_length_supported(int n) {
   return n == 32 || n == 48 || n == 64 || n == 96 || n == 128;
 }
 
-// Tile shapes of the batched passes per length and tile variant (0 default,
-// 2 narrow): columns per tile, threads, LDS bytes; row pairs per block,
-// threads, LDS bytes.  A batched launch takes the largest block and LDS of
-// the instances it covers.
+// Tile shapes of the batched x passes per length and tile variant (0 default,
+// 2 narrow): columns per tile, threads, LDS bytes.  A batched launch takes
+// the largest block and LDS of the instances it covers.
 template <typename T>
 struct BatchShape {
-  int B, col_threads, col_lds, G, row_threads, row_lds;
+  int B, col_threads, col_lds;
 };
 template <typename T, int N, int V>
 constexpr BatchShape<T> batch_shape_nv() {
-  return {ColShape<T, N, V>::B, ColShape<T, N, V>::THREADS, (int)(ColShape<T, N, V>::LDS * sizeof(cx<T>)),
-          RowShape<N, V>::G, RowShape<N, V>::THREADS,
-          (int)(RowShape<N, V>::G * RowShape<N, V>::LEN * sizeof(cx<T>))};
+  return {ColShape<T, N, V>::B, ColShape<T, N, V>::THREADS, (int)(ColShape<T, N, V>::LDS * sizeof(cx<T>))};
 }
 template <typename T>
 inline BatchShape<T> batch_shape(int n, int v) {
@@ -44,20 +41,15 @@ inline BatchShape<T> batch_shape(int n, int v) {
   case NN: return v == 2 ? batch_shape_nv<T, NN, 2>() : batch_shape_nv<T, NN, 0>();
     PL_BATCH_LENGTHS(PL_C)
 #undef PL_C
-    default: return {0, 0, 0, 0, 0, 0};
+    default: return {0, 0, 0};
   }
 }
 
-// work item: (instance, tile or row-pair block, slab, block index in the
-// instance); cls: the length class of every item of the launch (batch_class);
+// work item: (instance, tile, slab, block index in the instance); cls: the length class of every item of the launch (batch_class);
 // threads / lds_bytes: the launch's block size and dynamic LDS
 template <typename T>
 hipError_t launch_col_batch(bool inverse, int op, int cls, const ColArgs<T>* args, const int4* work, int nblocks,
                             int threads, int lds_bytes, hipStream_t st);
-template <typename T>
-hipError_t launch_row_batch(int op, int cls, const RowArgs<T>* args, const int4* work, int nblocks, int threads,
-                            int lds_bytes, hipStream_t st);
-
 // Per-instance operands of the batched elementwise kernels (grid.y = instance)
 template <typename T>
 struct BatchElem {

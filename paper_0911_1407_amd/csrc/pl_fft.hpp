@@ -220,6 +220,17 @@ PL_PLAN(256, 16, 2, 16, 16, 1)
 PL_PLAN(512, 32, 3, 8, 8, 8)
 #undef PL_PLAN
 
+// The same length with its radices in reverse: its stage-0 input slots are the
+// output slots of the plan above, so a forward transform by it can follow an
+// inverse one by the other without an exchange between them.
+template <class PL>
+struct RevPlan {
+  static constexpr int N = PL::N, P = PL::P, W = PL::W, NS = PL::NS;
+  static constexpr int R0 = NS == 1 ? PL::R0 : (NS == 2 ? PL::R1 : PL::R2);
+  static constexpr int R1 = NS == 1 ? 1 : (NS == 2 ? PL::R0 : PL::R1);
+  static constexpr int R2 = NS == 3 ? PL::R0 : 1;
+};
+
 template <class PL, int S>
 struct StageInfo {
   static constexpr int R = S == 0 ? PL::R0 : (S == 1 ? PL::R1 : PL::R2);

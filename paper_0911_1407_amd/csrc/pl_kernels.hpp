@@ -878,7 +878,6 @@ struct RowArgs {
   int model;           // ROW_GRAD likelihood: MODEL_LOGNORMAL or MODEL_GAUSSIAN
   const double* lb_d1;  // ROW_LB_OUT: the curvature diagonal and the kept field q
   const double* lb_q;
-  int variant;  // batched launches: this instance's tile variant (0 or 2)
   const double* scal;  // ROW_GRAD_STEP: device scalars (the step length)
   // plane passes (plane_body): rows per x plane, x planes, y twiddles
   int ny, nplanes;
@@ -918,11 +917,18 @@ __device__ __forceinline__ double grad_cell(const RowArgs<T>& a, long i, double 
 template <int N, int V = 0>
 struct RowShape {
   static constexpr int P = Plan<N>::P;
-  static constexpr int TH = V == 1 ? 512 : (V == 2 ? 128 : 256);
+  static constexpr int TH = V == 1 ? 512 : 256;
   static constexpr int G = (TH / P) > 32 ? 32 : (TH / P < 1 ? 1 : TH / P);  // row pairs per block
   static constexpr int THREADS = G * P;
   static constexpr int LEN = PaddedLen<N + 2, true>::value;  // LDS slots per pair
 };
+
+// which row operations leave partial sums, start from half rows, end in them
+constexpr bool row_has_sums(int op) {
+  return op == ROW_GRAD || op == ROW_GRAD_STEP || op == ROW_HVP || op == ROW_LB_IN || op == ROW_C2R_GRADLIK;
+}
+constexpr bool row_from_half(int op) { return op != ROW_R2C && op != ROW_GRAD_STEP; }
+constexpr bool row_to_half(int op) { return op != ROW_C2R && op != ROW_C2R_DIAG && op != ROW_C2R_GRADLIK; }
 
 // The Hessian diagonal at real cell i, in the transforms' precision.
 template <typename T>
@@ -938,6 +944,7 @@ __device__ __forceinline__ T diag_at(const RowArgs<T>& a, long i, int nt) {
 template <typename T, int N>
 struct BlockRowFft {
   using PL = Plan<N>;
+  using Fwd = PL;
   using MAP = LdsMap<1, true>;
   static constexpr bool PRELOAD_D = true, STREAM = true, GAUSS = true;
   int t;
@@ -952,16 +959,16 @@ struct BlockRowFft {
 };
 
 // One row pair's z transforms and pointwise work: thread t of the Plan<N>::P
-// sharing the pair; rowA, rowB: the two real rows; srcA / dst: the pair's
-// half rows (two rows of H values).  acc: the thread's partial sums.
+// sharing the pair; rowA, rowB: the two real rows; src / dst: their half rows.  acc: the thread's partial sums.
 template <typename T, int N, int OP, class FX>
 __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, const int t, const bool active,
                                          const bool valid, const long rowA, const long rowB, const cx<T>* srcA,
-                                         cx<T>* dst, double (&acc)[2]) {
-  using PL = Plan<N>;
+                                         const cx<T>* srcB, cx<T>* dstA, cx<T>* dstB, double (&acc)[2]) {
+  using PL = Plan<N>;              // inverse transforms
+  using PLF = typename FX::Fwd;    // forward ones
   constexpr int P = PL::P;
   constexpr int W = PL::W;
-  constexpr int R0 = PL::R0;
+  constexpr int R0 = row_from_half(OP) ? PL::R0 : PLF::R0;  // of the first transform
   constexpr int RL = LastStage<PL>::R;
   constexpr int H = N / 2 + 1;
 
@@ -981,7 +988,7 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
     for (int q = 0; q < W / R0; ++q)
 #pragma unroll
       for (int r = 0; r < R0; ++r) {
-        const int e = in_pos<PL, 0>(t, q, r);
+        const int e = in_pos<PLF, 0>(t, q, r);
         double l[2] = {0.0, 0.0};
         if (valid) {
 #pragma unroll
@@ -999,16 +1006,15 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
     for (int q = 0; q < W / R0; ++q)
 #pragma unroll
       for (int r = 0; r < R0; ++r) {
-        int e = in_pos<PL, 0>(t, q, r);
+        const int e = in_pos<PLF, 0>(t, q, r);
         const T ra = a.in_r[rowA * N + e], rb = a.in_r[rowB * N + e];
         v[q * R0 + r] = {valid ? ra : T(0), valid ? rb : T(0)};
       }
   } else {
-    // the two half rows A (at rowA * H) and B (next H values) give
+    // the two half rows A and B give
     // Z[e] = A[e] + i B[e], with A[e] = conj A[N - e] above N/2: each lane
     // loads its elements straight from memory (the lanes of a row pair read
     // consecutive, or mirrored consecutive, values)
-    const cx<T>* srcB = srcA + H;
 #pragma unroll
     for (int q = 0; q < W / R0; ++q)
 #pragma unroll
@@ -1208,39 +1214,32 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
   // split needs neither LDS nor a barrier.  All lanes take part in the
   // shuffles (uniform control flow); only valid ones store.
   {
-    constexpr int QL = W / RL;
+    constexpr int RF = LastStage<PLF>::R, QL = W / RF;
     const int lane = (int)(threadIdx.x & 63);
     const int src_lane = (lane & ~(P - 1)) | ((P - t) & (P - 1));
 #pragma unroll
     for (int j = 0; j <= W / 2; ++j) {
       const int jo = W - 1 - j;                   // partner slot (t > 0)
       const int jz = (W - j) % W;                 // own slot (t = 0)
-      const cx<T> send = v[(jo % QL) * RL + jo / QL];
+      const cx<T> send = v[(jo % QL) * RF + jo / QL];
       cx<T> zc;
       if constexpr (P > 1) {
         zc.x = __shfl(send.x, src_lane, 64);
         zc.y = __shfl(send.y, src_lane, 64);
-        if (t == 0) zc = v[(jz % QL) * RL + jz / QL];
+        if (t == 0) zc = v[(jz % QL) * RF + jz / QL];
       } else {
-        zc = v[(jz % QL) * RL + jz / QL];
+        zc = v[(jz % QL) * RF + jz / QL];
       }
-      const cx<T> zk = v[(j % QL) * RL + j / QL];
+      const cx<T> zk = v[(j % QL) * RF + j / QL];
       const int k = t + P * j;
       if (valid && k < H) {
-        dst[k] = {T(0.5) * (zk.x + zc.x), T(0.5) * (zk.y - zc.y)};
-        dst[H + k] = {T(0.5) * (zk.y + zc.y), T(0.5) * (zc.x - zk.x)};
+        dstA[k] = {T(0.5) * (zk.x + zc.x), T(0.5) * (zk.y - zc.y)};
+        dstB[k] = {T(0.5) * (zk.y + zc.y), T(0.5) * (zc.x - zk.x)};
       }
       fx.chunk(j);
     }
   }
 }
-
-// which row operations leave partial sums, start from half rows, end in them
-constexpr bool row_has_sums(int op) {
-  return op == ROW_GRAD || op == ROW_GRAD_STEP || op == ROW_HVP || op == ROW_LB_IN || op == ROW_C2R_GRADLIK;
-}
-constexpr bool row_from_half(int op) { return op != ROW_R2C && op != ROW_GRAD_STEP; }
-constexpr bool row_to_half(int op) { return op != ROW_C2R && op != ROW_C2R_DIAG && op != ROW_C2R_GRADLIK; }
 
 template <typename T, int N, int OP, int V = 0>
 __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>* lds_all, int block_linear) {
@@ -1257,7 +1256,9 @@ __device__ __forceinline__ void row_body(const RowArgs<T>& a, int ublock, cx<T>*
   const long rowA = 2L * uc, rowB = 2L * uc + 1;
   const BlockRowFft<T, N> fx{t, lds_all + ul * LEN, a.tw, active};
   double acc[2] = {0.0, 0.0};
-  row_core<T, N, OP>(a, fx, t, active, valid, rowA, rowB, a.in_c + rowA * H, a.out_c + rowA * H, acc);
+  const cx<T>* src = a.in_c + rowA * H;
+  cx<T>* dst = a.out_c + rowA * H;
+  row_core<T, N, OP>(a, fx, t, active, valid, rowA, rowB, src, src + H, dst, dst + H, acc);
   if constexpr (row_has_sums(OP)) block_reduce_store<2>(acc, a.partials, block_linear);
 }
 
@@ -1324,12 +1325,12 @@ __global__ void __launch_bounds__(RED_THREADS) cg_init_kernel(const cx<double>* 
   cg_init_body<T>(rhs, rhs_sign, x, r, p, tab, radial, g, nh, scal, partials, blockIdx.x, gridDim.x);
 }
 
-enum FinKind { FIN_STORE = 0, FIN_CG_INIT = 1, FIN_CG_ALPHA = 2, FIN_CG_BETA = 3, FIN_DBAR = 4, FIN_CG_ALPHA_ADD = 5,
+enum FinKind { FIN_STORE = 0, FIN_CG_INIT = 1, FIN_CG_BETA = 3, FIN_DBAR = 4, FIN_CG_ALPHA_ADD = 5,
                FIN_CG_STEP = 6, FIN_CG_CHECK = 7, FIN_CG_BETA_DEV = 8, FIN_CG_ALPHA_FIRST = 9,
                FIN_CG_ALPHA_K = 10, FIN_CG_BETA_K = 11 };
 
 // Sum partials[nb][K] in a fixed order; then scalar bookkeeping.
-// kind FIN_CG_ALPHA: p^H H p = scale2 * sum(partials2[nb2]) (prior part from
+// kind FIN_CG_ALPHA_ADD: p^H H p = scale2 * sum(partials2[nb2]) (prior part from
 // the first pass) + scale * sum(partials[nb][K], k = 0) (diagonal part).
 // Sum K interleaved per-block partials (src[i * K + k], i < n) over the
 // block: every thread keeps 4 K loads in flight per round over a fixed
@@ -1371,9 +1372,8 @@ __device__ __forceinline__ void fin_sums(const double* __restrict__ src, int n, 
 
 // Device-side reduction of per-block partials and the scalar bookkeeping
 // of the Krylov / Newton loops (kind: FinKind).  One block of NT threads.
-// DEVCOUNT: the batched CG's forms, with the iteration count in SC_ITS
-// (the alpha slot for aux < 0, FIN_CG_BETA_DEV); the single-grid callers
-// compile without them.
+// DEVCOUNT: the batched CG's form, with the iteration count in SC_ITS
+// (FIN_CG_BETA_DEV); the single-grid callers compile without it.
 template <int NT, bool DEVCOUNT>
 __device__ __forceinline__ void finalize_body(const double* __restrict__ partials, int nb, int K, int kind, int dst,
                                               double scale, double* __restrict__ scal, double aux,
@@ -1426,18 +1426,12 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       scal[SC_ALPHA] = 0.0;
       scal[SC_BETA] = 0.0;
       break;
-    case FIN_CG_ALPHA:
-    case FIN_CG_ALPHA_ADD: {  // _ADD: p^H H p also holds scal[dst]
+    case FIN_CG_ALPHA_ADD: {  // p^H H p also holds scal[dst]
       if (scal[SC_DONE] != 0.0) break;  // iteration skipped
-      const double pq = v[0] + extra + (kind == FIN_CG_ALPHA_ADD ? scal[dst] : 0.0);
+      const double pq = v[0] + extra + scal[dst];
       scal[SC_PQ] = pq;
-      // aux > 0: the slot holding r^H M^-1 r (cg_rz_slot); with DEVCOUNT and
-      // aux < 0: the slot of the iteration count in SC_ITS; else SC_RZ
-      int rz_at = aux > 0.0 ? (int)aux : (int)SC_RZ;
-      if constexpr (DEVCOUNT)
-        if (aux < 0.0) rz_at = cg_rz_slot((int)scal[SC_ITS]);
       double al = 0.0;
-      if (scal[SC_DONE] == 0.0 && pq > 0.0) al = scal[rz_at] / pq;
+      if (scal[SC_DONE] == 0.0 && pq > 0.0) al = scal[SC_RZ] / pq;
       if (scal[SC_DONE] == 0.0 && !(pq > 0.0)) scal[SC_DONE] = 2.0;  // breakdown
       scal[SC_ALPHA] = al;
       break;

@@ -293,6 +293,18 @@ RowArgs<T> row_args(pl_plan* p) {
   a.partials = p->partials;
   a.nt = p->var[sizeof(T) == 4 ? 1 : 0][V_NT];
   a.model = p->model;
+  a.ny = p->n[1];
+  a.nplanes = p->n[0];
+  a.tw_y = View<T>::tw(p, 1);
+  return a;
+}
+
+// A plane pass on the half spectrum buf, in place.
+template <typename T>
+RowArgs<T> plane_args(pl_plan* p, cx<T>* buf) {
+  RowArgs<T> a = row_args<T>(p);
+  a.in_c = buf;
+  a.out_c = buf;
   return a;
 }
 
@@ -339,9 +351,6 @@ int run_yz(pl_plan* p, int op, cx<T>* buf, RowArgs<T> ra, int* nb = nullptr) {
   ra.out_c = buf;
   int dummy;
   if (use_plane<T>(p, op)) {
-    ra.ny = p->n[1];
-    ra.nplanes = p->n[0];
-    ra.tw_y = View<T>::tw(p, 1);
     HIPCHK(p, launch_plane<T>(op, ra, p->stream, nb ? nb : &dummy));
     return PL_OK;
   }
@@ -1668,10 +1677,8 @@ extern "C" int pl_compare_fields_noalloc(const int32_t n[3], const double* rec, 
 }
 
 namespace pl {
-// Waves of a plane pass: its larger count of wave-sized groups of transforms
-// (64 / P columns, 64 / P row pairs), spread evenly over at most
-// PLANE_MAX_WAVES.
-int plane_waves(int ny, int nz) {
+// A plane's wave-sized groups of transforms: 64 / P columns, 64 / P row pairs.
+void plane_groups(int ny, int nz, int* cols, int* rows) {
   auto per_wave = [](int n) {
     switch (n) {
 #define PL_C(NN) case NN: return 64 / Plan<NN>::P;
@@ -1680,7 +1687,15 @@ int plane_waves(int ny, int nz) {
       default: return 64;
     }
   };
-  const int cols = (nz / 2 + per_wave(ny)) / per_wave(ny), rows = (ny / 2 + per_wave(nz) - 1) / per_wave(nz);
+  *cols = (nz / 2 + per_wave(ny)) / per_wave(ny);
+  *rows = (ny / 2 + per_wave(nz) - 1) / per_wave(nz);
+}
+
+// Waves of a plane pass: its larger count of groups, spread evenly over at
+// most PLANE_MAX_WAVES.
+int plane_waves(int ny, int nz) {
+  int cols, rows;
+  plane_groups(ny, nz, &cols, &rows);
   const int groups = std::max(cols, rows), rounds = (groups + PLANE_MAX_WAVES - 1) / PLANE_MAX_WAVES;
   return (groups + rounds - 1) / rounds;
 }
@@ -1975,10 +1990,10 @@ struct BWork {
   int threads[BATCH_CLASSES] = {0, 0}, lds[BATCH_CLASSES] = {0, 0};  // per class launch
   size_t off = 0, cap = 0;  // region in the blob and its capacity (items)
 };
-// W_XC / W_YC / W_RC: the running solve's CG passes over the instances not
+// W_XC / W_PC: the running solve's CG passes over the instances not
 // yet finished (rebuilt as they finish, so that the last CG steps do not
 // dispatch the blocks of finished grids)
-enum BWorkId { W_X64 = 0, W_Y64, W_R64, W_X32, W_Y32, W_R32, W_XC, W_YC, W_RC, W_COUNT };
+enum BWorkId { W_X64 = 0, W_P64, W_X32, W_P32, W_XC, W_PC, W_COUNT };
 
 void order_for_xcds(std::vector<int4>& nat) {
   std::vector<int4> w(nat.size());
@@ -1996,10 +2011,9 @@ void join_classes(BWork& w, std::vector<int4>* cls) {
   w.split = (int)cls[0].size();
 }
 
-// Column pass over all instances (axis 0: x, 1: y), instance i in tile
-// variant var[i].
+// x pass over all instances, instance i in tile variant var[i].
 template <typename T>
-void col_work(const std::vector<pl_plan*>& plans, int axis, const std::vector<int>& var, BWork& w,
+void col_work(const std::vector<pl_plan*>& plans, const std::vector<int>& var, BWork& w,
               const std::vector<int>* subset = nullptr) {
   std::vector<int4> cls[BATCH_CLASSES];
   w.nb.assign(plans.size(), 0);
@@ -2007,56 +2021,61 @@ void col_work(const std::vector<pl_plan*>& plans, int axis, const std::vector<in
   for (size_t i = 0; i < plans.size(); ++i) {
     if (subset && !(*subset)[i]) continue;
     const pl_plan* p = plans[i];
-    const int c = batch_class(p->n[axis]);
-    const BatchShape<T> sh = batch_shape<T>(p->n[axis], var[i]);
-    const int h = p->g.h;
-    const int ncols = axis == 0 ? p->n[1] * h : h;
-    const int nslabs = axis == 0 ? 1 : p->n[0];
-    const int nbx = (ncols + sh.B - 1) / sh.B;
-    for (int sl = 0; sl < nslabs; ++sl)
-      for (int t = 0; t < nbx; ++t) cls[c].push_back(make_int4((int)i, t, sl, t + nbx * sl));
-    w.nb[i] = nbx * nslabs;
+    const int c = batch_class(p->n[0]);
+    const BatchShape<T> sh = batch_shape<T>(p->n[0], var[i]);
+    const int nbx = (p->n[1] * p->g.h + sh.B - 1) / sh.B;
+    for (int t = 0; t < nbx; ++t) cls[c].push_back(make_int4((int)i, t, 0, t));
+    w.nb[i] = nbx;
     w.threads[c] = std::max(w.threads[c], sh.col_threads);
     w.lds[c] = std::max(w.lds[c], sh.col_lds);
   }
   join_classes(w, cls);
-  if (axis == 1) {
-    // one rider item per instance (tile -1) at the end of the first class's
-    // launch: the finalize that a y pass may carry (col_batch_kernel)
-    std::vector<int4> riders;
-    for (size_t i = 0; i < plans.size(); ++i)
-      if (!subset || (*subset)[i]) riders.push_back(make_int4((int)i, -1, 0, 0));
-    const bool first = w.split > 0;
-    w.items.insert(w.items.begin() + (first ? w.split : (long)w.items.size()), riders.begin(), riders.end());
-    if (first) w.split += (int)riders.size();
-  }
 }
 
-// Row (z) pass over all instances, instance i in tile variant var[i].
+// Waves that share a plane in a batched block of PLANE_BATCH_WAVES: the split
+// that finishes the most planes per unit of time, a plane taking the rounds of
+// its columns (twice, both y transforms) and of its row pairs.  (FP32 64 x 64:
+// two planes of 4 waves, 5 rounds, before one of 5 waves, 3 rounds.)
+int plane_batch_waves(int ny, int nz) {
+  int cols, rows, best = 1;
+  plane_groups(ny, nz, &cols, &rows);
+  double rate = 0.0;
+  for (int w = 1; w <= PLANE_BATCH_WAVES; ++w) {
+    const int rounds = 2 * ((cols + w - 1) / w) + (rows + w - 1) / w;
+    const double r = (double)(PLANE_BATCH_WAVES / w) / rounds;
+    if (r > rate * 1.0001) {
+      rate = r;
+      best = w;
+    }
+  }
+  return best;
+}
+
+// Plane pass over all instances.
 template <typename T>
-void row_work(const std::vector<pl_plan*>& plans, const std::vector<int>& var, BWork& w,
-              const std::vector<int>* subset = nullptr) {
+void plane_work(const std::vector<pl_plan*>& plans, BWork& w, const std::vector<int>* subset = nullptr) {
   std::vector<int4> cls[BATCH_CLASSES];
   w.nb.assign(plans.size(), 0);
   for (int c = 0; c < BATCH_CLASSES; ++c) w.threads[c] = w.lds[c] = 0;
   for (size_t i = 0; i < plans.size(); ++i) {
     if (subset && !(*subset)[i]) continue;
     const pl_plan* p = plans[i];
-    const int c = batch_class(p->n[2]);
-    const BatchShape<T> sh = batch_shape<T>(p->n[2], var[i]);
-    const int nunits = p->n[0] * p->n[1] / 2;
-    const int nbu = (nunits + sh.G - 1) / sh.G;
-    for (int b = 0; b < nbu; ++b) cls[c].push_back(make_int4((int)i, b, 0, b));
-    w.nb[i] = nbu;
-    w.threads[c] = std::max(w.threads[c], sh.row_threads);
-    w.lds[c] = std::max(w.lds[c], sh.row_lds);
+    const int c = plane_class(p->n[1], p->n[2]);
+    const size_t one = plane_lds_bytes(p->n[1], p->n[2], (int)sizeof(cx<T>));
+    int waves = plane_batch_waves(p->n[1], p->n[2]);
+    while ((PLANE_BATCH_WAVES / waves) * one > PLANE_LDS_MAX) ++waves;  // (one plane always fits)
+    const int per = PLANE_BATCH_WAVES / waves;
+    const int nb = (p->n[0] + per - 1) / per;
+    for (int t = 0; t < nb; ++t) cls[c].push_back(make_int4((int)i, t * per, waves, t));
+    w.nb[i] = nb;
+    w.lds[c] = std::max(w.lds[c], (int)(per * one));
   }
   join_classes(w, cls);
 }
 
-// Column / row pass kinds of a batched solve
-enum BCol { BC_SHAT_Y = 0, BC_SHAT_X, BC_G_XINV, BC_G_YINV, BC_G_YFWD, BC_G_XADD, BC_COUNT64 };
-enum BColT { BT_CG1 = 0, BT_CGYI, BT_CGYF, BT_CG5, BT_XCINV, BT_YCINV, BT_COUNT };
+// x and plane pass kinds of a batched solve
+enum BCol { BC_SHAT_X = 0, BC_G_XINV, BC_G_XADD, BC_COUNT64 };
+enum BColT { BT_CG1 = 0, BT_CG5, BT_XCINV, BT_COUNT };
 enum BRow { BR_R2C = 0, BR_GRAD, BR_COUNT64 };
 enum BRowT { BRT_HVP = 0, BRT_C2R, BRT_COUNT };
 enum BFin { BF_GRAD_ROW = 0, BF_GRAD_X, BF_INIT, BF_BETA, BF_LS, BF_COUNT };
@@ -2073,10 +2092,10 @@ struct pl_batch {
   size_t ws_bytes = 0, plans_bytes = 0, blob_bytes = 0;
   char* ws = nullptr;
   // work lists of the passes (BWorkId) and the tile variant of every
-  // instance's column and row passes per precision ([0] FP64, [1] FP32),
-  // chosen per grid length (pl_batch_autotune)
+  // instance's x passes per precision ([0] FP64, [1] FP32), chosen per grid
+  // length (pl_batch_autotune)
   BWork work[W_COUNT];
-  std::vector<int> vcol[2], vrow[2];
+  std::vector<int> vcol[2];
   // device blob and its host mirror
   char* d_blob = nullptr;
   char* h_blob = nullptr;
@@ -2161,27 +2180,24 @@ const int4* work_dev(pl_batch* b, int which) { return blob_ptr<int4>(b, b->work[
 // Work lists and launch shapes for the current tile variants, copied into
 // the host blob (uploaded with the pass arguments before each solve).
 void build_work(pl_batch* b) {
-  col_work<double>(b->plans, 0, b->vcol[0], b->work[W_X64]);
-  col_work<double>(b->plans, 1, b->vcol[0], b->work[W_Y64]);
-  row_work<double>(b->plans, b->vrow[0], b->work[W_R64]);
-  col_work<float>(b->plans, 0, b->vcol[1], b->work[W_X32]);
-  col_work<float>(b->plans, 1, b->vcol[1], b->work[W_Y32]);
-  row_work<float>(b->plans, b->vrow[1], b->work[W_R32]);
+  col_work<double>(b->plans, b->vcol[0], b->work[W_X64]);
+  plane_work<double>(b->plans, b->work[W_P64]);
+  col_work<float>(b->plans, b->vcol[1], b->work[W_X32]);
+  plane_work<float>(b->plans, b->work[W_P32]);
   if (b->h_blob)
     for (int i = 0; i < W_COUNT; ++i)
       if (!b->work[i].items.empty())
         std::memcpy(b->h_blob + b->work[i].off, b->work[i].items.data(), sizeof(int4) * b->work[i].items.size());
 }
 
-// The CG passes' work lists over the instances in `subset` (W_XC, W_YC,
-// W_RC), copied to the device on the batch's stream.
+// The CG passes' work lists over the instances in `subset` (W_XC, W_PC),
+// copied to the device on the batch's stream.
 template <typename T>
 int build_compact(pl_batch* b, const std::vector<int>& subset) {
   const int ti = sizeof(T) == 8 ? 0 : 1;
-  col_work<T>(b->plans, 0, b->vcol[ti], b->work[W_XC], &subset);
-  col_work<T>(b->plans, 1, b->vcol[ti], b->work[W_YC], &subset);
-  row_work<T>(b->plans, b->vrow[ti], b->work[W_RC], &subset);
-  for (int i : {(int)W_XC, (int)W_YC, (int)W_RC}) {
+  col_work<T>(b->plans, b->vcol[ti], b->work[W_XC], &subset);
+  plane_work<T>(b->plans, b->work[W_PC], &subset);
+  for (int i : {(int)W_XC, (int)W_PC}) {
     BWork& w = b->work[i];
     if (w.items.empty() || w.items.size() > w.cap) return PL_ERR_INVALID_ARG;
     std::memcpy(b->h_blob + w.off, w.items.data(), sizeof(int4) * w.items.size());
@@ -2194,11 +2210,9 @@ int build_compact(pl_batch* b, const std::vector<int>& subset) {
 template <typename T>
 int wid_x() { return sizeof(T) == 8 ? W_X64 : W_X32; }
 template <typename T>
-int wid_y() { return sizeof(T) == 8 ? W_Y64 : W_Y32; }
-template <typename T>
-int wid_r() { return sizeof(T) == 8 ? W_R64 : W_R32; }
+int wid_p() { return sizeof(T) == 8 ? W_P64 : W_P32; }
 
-// One batched column / row pass over work list `wid`: one launch per length
+// One batched x / plane pass over work list `wid`: one launch per length
 // class present.
 template <typename T>
 hipError_t bcol(pl_batch* b, bool inverse, int op, const ColArgs<T>* args, int wid) {
@@ -2213,13 +2227,12 @@ hipError_t bcol(pl_batch* b, bool inverse, int op, const ColArgs<T>* args, int w
   return hipSuccess;
 }
 template <typename T>
-hipError_t brow(pl_batch* b, int op, const RowArgs<T>* args, int wid) {
+hipError_t bplane(pl_batch* b, int op, const RowArgs<T>* args, int wid) {
   const BWork& w = b->work[wid];
   const int count[2] = {w.split, (int)w.items.size() - w.split};
   for (int c = 0, first = 0; c < BATCH_CLASSES; first += count[c], ++c) {
     if (count[c] == 0) continue;
-    hipError_t e = launch_row_batch<T>(op, c, args, work_dev(b, wid) + first, count[c], w.threads[c], w.lds[c],
-                                       b->stream);
+    hipError_t e = launch_plane_batch<T>(op, c, args, work_dev(b, wid) + first, count[c], w.lds[c], b->stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -2233,18 +2246,11 @@ void fill_args(pl_batch* b, double* const* s_io) {
     const double* inactive = p->scal + SC_INACTIVE;
     const double* done = p->scal + SC_DONE;
     // FP64 gradient and transforms of s
-    const int v64 = b->vcol[0][i], r64 = b->vrow[0][i];
-    const int vT = b->vcol[sizeof(T) == 4 ? 1 : 0][i], rT = b->vrow[sizeof(T) == 4 ? 1 : 0][i];
+    const int v64 = b->vcol[0][i], vT = b->vcol[sizeof(T) == 4 ? 1 : 0][i];
     ColArgs<double>* c;
-    c = &cargs64(b, BC_SHAT_Y, true)[i]; *c = col_args<double>(p, 1, p->s_hat, p->s_hat); c->skip = inactive;
-    c->variant = v64;
     c = &cargs64(b, BC_SHAT_X, true)[i]; *c = col_args<double>(p, 0, p->s_hat, p->s_hat); c->skip = inactive;
     c->variant = v64;
     c = &cargs64(b, BC_G_XINV, true)[i]; *c = col_args<double>(p, 0, p->s_hat, p->t64); c->skip = inactive;
-    c->variant = v64;
-    c = &cargs64(b, BC_G_YINV, true)[i]; *c = col_args<double>(p, 1, p->t64, p->t64); c->skip = inactive;
-    c->variant = v64;
-    c = &cargs64(b, BC_G_YFWD, true)[i]; *c = col_args<double>(p, 1, p->t64, p->t64); c->skip = inactive;
     c->variant = v64;
     c = &cargs64(b, BC_G_XADD, true)[i]; *c = col_args<double>(p, 0, p->t64, p->g_hat); c->skip = inactive;
     c->variant = v64;
@@ -2255,11 +2261,9 @@ void fill_args(pl_batch* b, double* const* s_io) {
     c->base = p->s_hat;
     c->k0_shift = (double)p->N * p->prob.mu;
     RowArgs<double>* r;
-    r = &rargs64(b, BR_R2C, true)[i]; *r = row_args<double>(p); r->in_r = s_io[i]; r->out_c = p->s_hat; r->skip = inactive;
-    r->variant = r64;
-    r = &rargs64(b, BR_GRAD, true)[i]; *r = row_args<double>(p); r->in_c = p->t64; r->out_c = p->t64;
+    r = &rargs64(b, BR_R2C, true)[i]; *r = plane_args<double>(p, p->s_hat); r->in_r = s_io[i]; r->skip = inactive;
+    r = &rargs64(b, BR_GRAD, true)[i]; *r = plane_args<double>(p, p->t64);
     r->s_out = s_io[i]; r->e_out = p->e; r->d_out = p->d; r->skip = inactive;
-    r->variant = r64;
     // Krylov passes in T
     cx<T>*x = View<T>::x(p), *rr = View<T>::r(p), *pp = View<T>::pv(p), *t = View<T>::t(p);
     double* part_a = p->partials;
@@ -2275,31 +2279,32 @@ void fill_args(pl_batch* b, double* const* s_io) {
     ct->beta_scale = 1.0 / (double)p->N;
     ct->radial = p->radial ? TAB_SHELL : TAB_MODE;
     ct->inv_lam = View<T>::tab(p, p->radial);
-    ct = &cargs_t<T>(b, BT_CGYI, true)[i]; *ct = col_args<T>(p, 1, t, t); ct->skip = done; ct->variant = vT;
-    ct = &cargs_t<T>(b, BT_CGYF, true)[i]; *ct = col_args<T>(p, 1, t, t); ct->skip = done; ct->variant = vT;
     ct = &cargs_t<T>(b, BT_CG5, true)[i]; *ct = col_args<T>(p, 0, t, t);
     ct->base = pp; ct->cg_r = rr; ct->cg_x = x; ct->scal = p->scal; ct->partials = part_c; ct->skip = done;
     ct->variant = vT;  // (the last pass advances SC_ITS after each iteration)
     ct->radial = p->radial ? TAB_SHELL : TAB_MODE;
     ct->inv_lam = View<T>::tab(p, p->radial);
     ct = &cargs_t<T>(b, BT_XCINV, true)[i]; *ct = col_args<T>(p, 0, x, t); ct->skip = inactive; ct->variant = vT;
-    ct = &cargs_t<T>(b, BT_YCINV, true)[i]; *ct = col_args<T>(p, 1, t, t); ct->skip = inactive; ct->variant = vT;
     RowArgs<T>* rt;
-    rt = &rargs_t<T>(b, BRT_HVP, true)[i]; *rt = row_args<T>(p); rt->in_c = t; rt->out_c = t;
-    rt->partials = part_b; rt->skip = done; rt->variant = rT;
-    rt = &rargs_t<T>(b, BRT_C2R, true)[i]; *rt = row_args<T>(p); rt->in_c = t; rt->out_r = View<T>::preal(p);
-    rt->skip = inactive; rt->variant = rT;
+    rt = &rargs_t<T>(b, BRT_HVP, true)[i]; *rt = plane_args<T>(p, t);
+    rt->partials = part_b; rt->skip = done;
+    rt = &rargs_t<T>(b, BRT_C2R, true)[i]; *rt = plane_args<T>(p, t); rt->out_r = View<T>::preal(p);
+    rt->skip = inactive;
     // finalize records
     const std::vector<int>& nbx = b->work[wid_x<T>()].nb;
-    const std::vector<int>& nbr = b->work[wid_r<T>()].nb;
+    const std::vector<int>& nbp = b->work[wid_p<T>()].nb;
     const double invN = 1.0 / (double)p->N;
-    fins(b, BF_GRAD_ROW, true)[i] = BatchFin{part_a, b->work[W_R64].nb[i], nullptr, 0, p->scal, invN};
+    fins(b, BF_GRAD_ROW, true)[i] = BatchFin{part_a, b->work[W_P64].nb[i], nullptr, 0, p->scal, invN};
     fins(b, BF_GRAD_X, true)[i] = BatchFin{part_a, b->work[W_X64].nb[i], nullptr, 0, p->scal, invN};
     fins(b, BF_INIT, true)[i] = BatchFin{part_a, NBB, nullptr, 0, p->scal, invN};
-    // alpha = r^H z / p^H H p, finalized by a rider of the forward y pass
-    ColArgs<T>* cyf = &cargs_t<T>(b, BT_CGYF, true)[i];
-    cyf->fin_on = 1;
-    cyf->fin = FinArgs{part_b, nbr[i], 2, FIN_CG_ALPHA, 0, 1.0, p->scal, -1.0, part_a, nbx[i], invN};
+    // the last pass forms alpha itself, from the plane pass's and the first
+    // pass's sums
+    ColArgs<T>& last = cargs_t<T>(b, BT_CG5, true)[i];
+    last.z_part = part_b;
+    last.z_nb = nbp[i];
+    last.beta_part = part_a;
+    last.beta_nb = nbx[i];
+    last.beta_scale = invN;
     fins(b, BF_BETA, true)[i] = BatchFin{part_c, nbx[i], nullptr, 0, p->scal, invN};
     cargs_t<T>(b, BT_CG1, true)[i].beta_nb = nbx[i];
     fins(b, BF_LS, true)[i] = BatchFin{part_a, NBB, nullptr, 0, p->scal, invN};
@@ -2364,24 +2369,19 @@ int belem_upload(pl_batch* b) {
 
 int bgrad(pl_batch* b) {
   BHIP(b, bcol<double>(b, true, COL_PLAIN, cargs64(b, BC_G_XINV, false), W_X64));
-  BHIP(b, bcol<double>(b, true, COL_PLAIN, cargs64(b, BC_G_YINV, false), W_Y64));
-  BHIP(b, brow<double>(b, ROW_GRAD, rargs64(b, BR_GRAD, false), W_R64));
+  BHIP(b, bplane<double>(b, ROW_GRAD, rargs64(b, BR_GRAD, false), W_P64));
   int rc = bfin(b, BF_GRAD_ROW, 2, FIN_STORE, SC_LIK, 1.0, 0);
   if (rc) return rc;
-  BHIP(b, bcol<double>(b, false, COL_PLAIN, cargs64(b, BC_G_YFWD, false), W_Y64));
   BHIP(b, bcol<double>(b, false, COL_ADDPRIOR, cargs64(b, BC_G_XADD, false), W_X64));
   return bfin(b, BF_GRAD_X, 3, FIN_STORE, SC_GG - 1, 0.0, 1);
 }
 
 // Enqueue `chunk` fused CG steps for all instances (captured in a graph)
 template <typename T>
-int bcg_chunk(pl_batch* b, int chunk, int max_cg, int wx = wid_x<T>(), int wy = wid_y<T>(), int wr = wid_r<T>()) {
+int bcg_chunk(pl_batch* b, int chunk, int max_cg, int wx = wid_x<T>(), int wp = wid_p<T>()) {
   for (int k = 0; k < chunk; ++k) {
     BHIP(b, bcol<T>(b, true, COL_CG_FIRST, cargs_t<T>(b, BT_CG1, false), wx));
-    BHIP(b, bcol<T>(b, true, COL_PLAIN, cargs_t<T>(b, BT_CGYI, false), wy));
-    BHIP(b, brow<T>(b, ROW_HVP, rargs_t<T>(b, BRT_HVP, false), wr));
-    // the forward y pass carries the alpha finalize (a rider per instance)
-    BHIP(b, bcol<T>(b, false, COL_PLAIN, cargs_t<T>(b, BT_CGYF, false), wy));
+    BHIP(b, bplane<T>(b, ROW_HVP, rargs_t<T>(b, BRT_HVP, false), wp));
     BHIP(b, bcol<T>(b, false, COL_CG_LAST, cargs_t<T>(b, BT_CG5, false), wx));
   }
   // the next first pass closes each iteration; after the chunk one finalize
@@ -2408,8 +2408,7 @@ int batch_newton(pl_batch* b, double* const* s_io, const pl_solve_opts& o, pl_so
   int rc = bctl(b);
   if (rc) return rc;
   // s_hat = F s0, then the gradient
-  BHIP(b, brow<double>(b, ROW_R2C, rargs64(b, BR_R2C, false), W_R64));
-  BHIP(b, bcol<double>(b, false, COL_PLAIN, cargs64(b, BC_SHAT_Y, false), W_Y64));
+  BHIP(b, bplane<double>(b, ROW_R2C, rargs64(b, BR_R2C, false), W_P64));
   BHIP(b, bcol<double>(b, false, COL_PLAIN, cargs64(b, BC_SHAT_X, false), W_X64));
   rc = bgrad(b);
   if (rc) return rc;
@@ -2537,8 +2536,7 @@ int batch_newton(pl_batch* b, double* const* s_io, const pl_solve_opts& o, pl_so
       rc = belem_upload<T>(b);
       if (rc) return rc;
       BHIP(b, bcol<T>(b, true, COL_PLAIN, cargs_t<T>(b, BT_XCINV, false), wid_x<T>()));
-      BHIP(b, bcol<T>(b, true, COL_PLAIN, cargs_t<T>(b, BT_YCINV, false), wid_y<T>()));
-      BHIP(b, brow<T>(b, ROW_C2R, rargs_t<T>(b, BRT_C2R, false), wid_r<T>()));
+      BHIP(b, bplane<T>(b, ROW_C2R, rargs_t<T>(b, BRT_C2R, false), wid_p<T>()));
       hipLaunchKernelGGL((ls_dots_batch_kernel<T>), dim3(NBB, K), dim3(RED_THREADS), 0, b->stream,
                          elems<T>(b, false));
       BHIP(b, hipGetLastError());
@@ -2725,7 +2723,7 @@ int batch_newton(pl_batch* b, double* const* s_io, const pl_solve_opts& o, pl_so
     // graph for each would keep the GPU idle while the host does it, where
     // direct launches are issued while the GPU runs the previous ones
     if (compacted) {
-      rc = bcg_chunk<T>(b, o.check_every, o.max_cg, W_XC, W_YC, W_RC);
+      rc = bcg_chunk<T>(b, o.check_every, o.max_cg, W_XC, W_PC);
       if (rc) return rc;
     } else {
       BHIP(b, hipGraphLaunch(cg_graph, b->stream));
@@ -2773,8 +2771,7 @@ int batch_newton(pl_batch* b, double* const* s_io, const pl_solve_opts& o, pl_so
   return first_bad;
 }
 
-// Time one batched CG step (the seven launches of bcg_chunk over every
-// instance) with the current tile variants, average of `reps`; on hashed
+// Time one batched CG step (the launches of bcg_chunk over every instance) with the current tile variants, average of `reps`; on hashed
 // Krylov vectors and Hessian diagonals, so nothing is left in a meaningful
 // state.
 template <typename T>
@@ -2832,15 +2829,10 @@ std::vector<int> batch_lengths(const pl_batch* b) {
   return out;
 }
 
-// Per length L: the tile variant of the column passes and of the row pass
-// of every instance whose axes have length L (an instance with uneven axes
-// takes the variant of its x length).
-void set_length_variant(pl_batch* b, int ti, int L, int vc, int vr) {
+// The tile variant of the x passes of every instance whose x axis has length L.
+void set_length_variant(pl_batch* b, int ti, int L, int vc) {
   for (int i = 0; i < b->K; ++i)
-    if (b->plans[i]->n[0] == L) {
-      b->vcol[ti][i] = vc;
-      b->vrow[ti][i] = vr;
-    }
+    if (b->plans[i]->n[0] == L) b->vcol[ti][i] = vc;
 }
 
 template <typename T>
@@ -2869,7 +2861,7 @@ int tune_batch_precision(pl_batch* b, const std::string& key, const std::vector<
     bool ok = true;
     for (size_t j = 0; j < nl; ++j) ok = ok && (vc[j] == 0 || vc[j] == 2) && (vr[j] == 0 || vr[j] == 2);
     if (!ok) continue;
-    for (size_t j = 0; j < nl; ++j) set_length_variant(b, ti, lens[j], vc[j], vr[j]);
+    for (size_t j = 0; j < nl; ++j) set_length_variant(b, ti, lens[j], vc[j]);
     return PL_OK;
   }
   // a positive Hessian diagonal for the timing runs
@@ -2882,31 +2874,28 @@ int tune_batch_precision(pl_batch* b, const std::string& key, const std::vector<
   }
   const int reps = 10;
   float best = 0.f;
-  for (size_t j = 0; j < nl; ++j) set_length_variant(b, ti, lens[j], 0, 0);
+  for (size_t j = 0; j < nl; ++j) set_length_variant(b, ti, lens[j], 0);
   int rc = time_batch_cg<T>(b, reps, &best);
   if (rc) return rc;
-  std::vector<int> kc(nl, 0), kr(nl, 0);
+  std::vector<int> kc(nl, 0);
   // one length at a time, the lengths holding the most cells first
   for (size_t j = 0; j < nl; ++j) {
-    for (int c = 0; c < 4; ++c) {
-      const int vc = (c & 1) ? 2 : 0, vr = (c & 2) ? 2 : 0;
-      if (vc == kc[j] && vr == kr[j]) continue;
-      set_length_variant(b, ti, lens[j], vc, vr);
-      float ms = 0.f;
-      rc = time_batch_cg<T>(b, reps, &ms);
-      if (rc) return rc;
-      if (ms < best) {
-        best = ms;
-        kc[j] = vc;
-        kr[j] = vr;
-      }
+    set_length_variant(b, ti, lens[j], 2);
+    float ms = 0.f;
+    rc = time_batch_cg<T>(b, reps, &ms);
+    if (rc) return rc;
+    if (ms < best) {
+      best = ms;
+      kc[j] = 2;
     }
-    set_length_variant(b, ti, lens[j], kc[j], kr[j]);
+    set_length_variant(b, ti, lens[j], kc[j]);
   }
+  // (the second list is the z passes' of caches written before the plane
+  // passes; there is nothing to choose there now)
   std::string line = key + " ";
   for (size_t j = 0; j < nl; ++j) line += (j ? "," : "") + std::to_string(kc[j]);
   line += " ";
-  for (size_t j = 0; j < nl; ++j) line += (j ? "," : "") + std::to_string(kr[j]);
+  for (size_t j = 0; j < nl; ++j) line += j ? ",0" : "0";
   char buf[32];
   std::snprintf(buf, sizeof(buf), " %.4f", (double)best);
   lines.push_back(line + buf);
@@ -2950,19 +2939,12 @@ int pl_batch_create(pl_batch** out, int n_inst, const int32_t* n, const double* 
   b->plans_bytes = off;
   // work-list capacities: every instance in the narrow variant (the most
   // blocks per pass); then the default variants
-  for (int t = 0; t < 2; ++t) {
-    b->vcol[t].assign(n_inst, 2);
-    b->vrow[t].assign(n_inst, 2);
-  }
+  for (int t = 0; t < 2; ++t) b->vcol[t].assign(n_inst, 2);
   build_work(b);
   for (int i = 0; i < W_COUNT; ++i) b->work[i].cap = b->work[i].items.size();
   b->work[W_XC].cap = std::max(b->work[W_X64].cap, b->work[W_X32].cap);
-  b->work[W_YC].cap = std::max(b->work[W_Y64].cap, b->work[W_Y32].cap);
-  b->work[W_RC].cap = std::max(b->work[W_R64].cap, b->work[W_R32].cap);
-  for (int t = 0; t < 2; ++t) {
-    b->vcol[t].assign(n_inst, 0);
-    b->vrow[t].assign(n_inst, 0);
-  }
+  b->work[W_PC].cap = std::max(b->work[W_P64].cap, b->work[W_P32].cap);
+  for (int t = 0; t < 2; ++t) b->vcol[t].assign(n_inst, 0);
   build_work(b);
   b->blob_bytes = batch_layout(b);
   b->ws_bytes = b->plans_bytes + b->blob_bytes;

@@ -25,5 +25,9 @@ hipError_t launch_row(int N, int op, const RowArgs<T>& a, hipStream_t st, int* n
 // a.ny rows of a.n cells, each plane in one workgroup's LDS.
 template <typename T>
 hipError_t launch_plane(int op, const RowArgs<T>& a, hipStream_t st, int* nblocks);
+// The batched form over a work list of one length class (plane_class).
+template <typename T>
+hipError_t launch_plane_batch(int op, int cls, const RowArgs<T>* args, const int4* work, int nblocks, int lds_bytes,
+                              hipStream_t st);
 
 }  // namespace pl

@@ -18,6 +18,8 @@
 // step beside the lanes that own it (the same values to the same places), so
 // the code has no branches on them; only their partial sums are dropped.
 #pragma once
+#include <type_traits>
+
 #include "pl_kernels.hpp"
 
 namespace pl {
@@ -40,21 +42,97 @@ __device__ __forceinline__ int per_round(int t) {
 
 constexpr int log2_of(int r) { return r <= 1 ? 0 : 1 + log2_of(r / 2); }
 
+// Storage of a row pair: two plane rows of `pitch` complex slots hold the N
+// elements of its exchanges, one slot left free after every 2^SHIFT so that
+// lanes a radix apart meet different LDS banks.
+template <int N>
+struct RowPad {
+  static constexpr int SHIFT = Plan<N>::R0 >= 16 ? 4 : 3;
+  static constexpr int LEN = Plan<N>::P == 1 ? N : N + (N >> SHIFT);
+  static constexpr int off(int e) { return e + (e >> SHIFT); }
+};
+// Complex slots between plane rows of nz cells: the half row (and half a row
+// pair's exchange storage), then up to a pitch whose rows fall on different
+// banks for the lanes that read a column together.
+constexpr int plane_pitch(int nz) {
+  switch (nz) {
+    case 32: return 18;
+    case 48: return 27;
+    case 64: return 36;
+    case 96: return 54;
+    case 128: return 68;
+    case 256: return 136;
+    default: return nz / 2 + 1;
+  }
+}
+
+// Element positions as compile-time functions (see in_pos / out_pos).
+template <class PL, int S>
+constexpr int pos_in(int t, int q, int r) {
+  return t + PL::P * q + r * (PL::N / StageInfo<PL, S>::R);
+}
+template <class PL, int S>
+constexpr int pos_out(int t, int q, int m) {
+  constexpr int R = StageInfo<PL, S>::R, Ns = StageInfo<PL, S>::NS;
+  const int j = t + PL::P * q, k = j % Ns;
+  return (j - k) * R + k + m * Ns;
+}
+// Whether OFF(position of slot (q, m)) is a part of the thread's plus a part of
+// the slot's, for every thread: then an exchange costs one address per thread
+// and the slots are instruction offsets.  (Not so where a radix of 3 or 6 meets
+// the padding: the first exchange of the reversed 48 and 96 plans.)
+template <class OFF, class PL, int S, bool OUT>
+constexpr bool splits() {
+  constexpr int R = StageInfo<PL, S>::R;
+  for (int t = 0; t < PL::P; ++t)
+    for (int q = 0; q < PL::W / R; ++q)
+      for (int m = 0; m < R; ++m) {
+        const int e = OUT ? pos_out<PL, S>(t, q, m) : pos_in<PL, S>(t, q, m);
+        const int et = OUT ? pos_out<PL, S>(t, 0, 0) : pos_in<PL, S>(t, 0, 0);
+        const int es = OUT ? pos_out<PL, S>(0, q, m) : pos_in<PL, S>(0, q, m);
+        if (OFF::at(e) != OFF::at(et) + OFF::at(es)) return false;
+      }
+  return true;
+}
+template <int N>
+struct RowOff {
+  static constexpr int at(int e) { return RowPad<N>::off(e); }
+  __device__ __forceinline__ int operator()(int e) const { return at(e); }
+};
+// (a column's elements lie `pitch` apart; H: the pitch, or 0 where it is only
+// known at run time)
+template <int H>
+struct ColOff {
+  int pitch;
+  static constexpr int at(int e) { return e * (H ? H : 1); }
+  __device__ __forceinline__ int operator()(int e) const { return e * (H ? H : pitch); }
+};
+
 // Move a transform's elements from stage SA's output slots to the input
 // slots of stage SB through its LDS storage (off: element -> slot).
 template <class PL, int SA, int SB, class OFF, typename T>
 __device__ __forceinline__ void wave_exchange(cx<T>* v, int t, cx<T>* lds, const OFF& off) {
   constexpr int RA = StageInfo<PL, SA>::R, RB = StageInfo<PL, SB>::R;
   wave_sync();
+  if constexpr (splits<OFF, PL, SA, true>()) {
+    cx<T>* to = lds + off(out_pos<PL, SA>(t, 0, 0));
 #pragma unroll
-  for (int q = 0; q < PL::W / RA; ++q)
+    for (int q = 0; q < PL::W / RA; ++q)
 #pragma unroll
-    for (int m = 0; m < RA; ++m) lds[off(out_pos<PL, SA>(t, q, m))] = v[q * RA + m];
+      for (int m = 0; m < RA; ++m) to[off(out_pos<PL, SA>(0, q, m))] = v[q * RA + m];
+  } else {
+#pragma unroll
+    for (int q = 0; q < PL::W / RA; ++q)
+#pragma unroll
+      for (int m = 0; m < RA; ++m) lds[off(out_pos<PL, SA>(t, q, m))] = v[q * RA + m];
+  }
   wave_sync();
+  static_assert(splits<OFF, PL, SB, false>(), "exchange addresses");
+  const cx<T>* from = lds + off(in_pos<PL, SB>(t, 0, 0));
 #pragma unroll
   for (int q = 0; q < PL::W / RB; ++q)
 #pragma unroll
-    for (int r = 0; r < RB; ++r) v[q * RB + r] = lds[off(in_pos<PL, SB>(t, q, r))];
+    for (int r = 0; r < RB; ++r) v[q * RB + r] = from[off(in_pos<PL, SB>(0, q, r))];
   wave_sync();
 }
 
@@ -77,19 +155,10 @@ __device__ __forceinline__ void wave_fft(cx<T>* v, int t, cx<T>* lds, const cx<T
   }
 }
 
-// A row pair's exchange slots: its two stored rows are one run of N + 2
-// complex slots.  The stage-0 writes of neighbouring lanes lie R0 slots
-// apart, which would fall on the same LDS banks; exchanging the low three
-// bits with the bits above log2(R0) spreads them (a permutation of every
-// aligned group of 8, so it stays inside the row).
-template <int R0>
-struct RowSlot {
-  __device__ __forceinline__ int operator()(int e) const { return e ^ ((e >> log2_of(R0)) & 7); }
-};
-
 template <typename T, int N>
 struct WaveRowFft {
   using PL = Plan<N>;
+  using Fwd = RevPlan<PL>;  // takes over the inverse transform's slots
   // two diagonal values per held element: beyond 8 FP64 elements they would
   // not leave registers for the twiddles
   static constexpr bool PRELOAD_D = sizeof(T) == 4 || PL::W <= 8, STREAM = false;
@@ -109,53 +178,52 @@ struct WaveRowFft {
   __device__ __forceinline__ void pin(double (&acc)[2]) const { asm volatile("" : "+v"(acc[0]), "+v"(acc[1])); }
   template <bool INV>
   __device__ __forceinline__ void fft(cx<T>* v) const {
-    wave_fft<PL, INV>(v, per_round(t), lds, tw, RowSlot<PL::R0>{});
+    using PX = std::conditional_t<INV, PL, Fwd>;
+    wave_fft<PX, INV>(v, per_round(t) & (PL::P - 1), lds, tw, RowOff<N>{});
   }
-  __device__ __forceinline__ void turn(cx<T>* v) const {
-    constexpr int RL = LastStage<PL>::R;
-    if constexpr (RL == PL::R0) {
-    } else if constexpr (PL::P == 1) {
-      last_to_first<PL, LdsMap<1, false>>(v, t, lds);
-    } else {
-      wave_exchange<PL, PL::NS - 1, 0>(v, t, lds, RowSlot<PL::R0>{});
-    }
-  }
+  __device__ __forceinline__ void turn(cx<T>*) const {}
 };
 
 // y transforms of a plane, wave `wave` of `nwaves`.  INV: from the half
-// spectrum in memory into the plane in LDS; else from LDS to memory.
-template <typename T, int N, bool INV>
-__device__ __forceinline__ void plane_cols(const cx<T>* __restrict__ src, cx<T>* __restrict__ dst, cx<T>* plane, int h,
-                                           const cx<T>* __restrict__ tw, int wave, int nwaves) {
+// spectrum in memory into the plane in LDS; else from LDS to memory.  HC: the
+// half row's length where it is known at compile time (square planes), so that
+// every LDS access is one address and an instruction offset; else 0.
+template <typename T, int N, bool INV, int HC>
+__device__ __forceinline__ void plane_cols(const cx<T>* __restrict__ src, cx<T>* __restrict__ dst, cx<T>* plane,
+                                           int h_, int pitch_, const cx<T>* __restrict__ tw, int wave, int nwaves) {
   using PL = Plan<N>;
   constexpr int P = PL::P, W = PL::W, C = 64 / P, R0 = PL::R0, RL = LastStage<PL>::R;
+  constexpr int PC = HC ? plane_pitch(2 * (HC - 1)) : 0;
+  const int h = HC ? HC : h_;
+  const ColOff<PC> off{pitch_};
   const int lane = threadIdx.x & 63, cl = lane % C;
-  const auto off = [h](int e) { return e * h; };
   for (int g = wave; g * C < h; g += nwaves) {
-    const int t = per_round(lane / C);
+    const int t = per_round(lane / C) & (P - 1);
     const int c = min(g * C + cl, h - 1);
     cx<T>* col = plane + c;
+    const cx<T>* first = col + off(t);
     cx<T> v[W];
 #pragma unroll
     for (int q = 0; q < W / R0; ++q)
 #pragma unroll
       for (int r = 0; r < R0; ++r) {
-        const int e = in_pos<PL, 0>(t, q, r);
+        const int e = in_pos<PL, 0>(0, q, r);
         if constexpr (INV)
-          v[q * R0 + r] = src[e * h + c];
+          v[q * R0 + r] = src[(t + e) * h + c];
         else
-          v[q * R0 + r] = col[e * h];
+          v[q * R0 + r] = first[off(e)];
       }
     wave_fft<PL, INV>(v, t, col, tw, off);
+    cx<T>* last = col + off(t);
 #pragma unroll
     for (int q = 0; q < W / RL; ++q)
 #pragma unroll
       for (int m = 0; m < RL; ++m) {
-        const int e = out_pos<PL, PL::NS - 1>(t, q, m);
+        const int e = out_pos<PL, PL::NS - 1>(0, q, m);
         if constexpr (INV)
-          col[e * h] = v[q * RL + m];
+          last[off(e)] = v[q * RL + m];
         else
-          dst[e * h + c] = v[q * RL + m];
+          dst[(t + e) * h + c] = v[q * RL + m];
       }
   }
 }
@@ -165,17 +233,18 @@ template <typename T, int N, int OP>
 __device__ __forceinline__ void plane_rows(const RowArgs<T>& a, cx<T>* plane, long row0, int wave, int nwaves,
                                            double (&acc)[2]) {
   using PL = Plan<N>;
-  constexpr int P = PL::P, U = 64 / P, H = N / 2 + 1;
+  constexpr int P = PL::P, U = 64 / P, H = plane_pitch(N);
+  static_assert(2 * H >= RowPad<N>::LEN && H >= N / 2 + 1, "row pair storage");
   const int lane = threadIdx.x & 63, ul = lane / P;
   const int pairs = a.ny >> 1;
   for (int g = wave; g * U < pairs; g += nwaves) {
-    const int t = per_round(lane % P);
+    const int t = per_round(lane % P) & (P - 1);
     const int u = min(g * U + ul, pairs - 1);
     cx<T>* rows = plane + 2 * u * H;
     const WaveRowFft<T, N> fx{t, rows, a.tw};
     const long rowA = row0 + 2 * u;
     double part[2] = {0.0, 0.0};
-    row_core<T, N, OP>(a, fx, t, true, true, rowA, rowA + 1, rows, rows, part);
+    row_core<T, N, OP>(a, fx, t, true, true, rowA, rowA + 1, rows, rows + H, rows, rows + H, part);
     if (g * U + ul < pairs) {
       acc[0] += part[0];
       acc[1] += part[1];
@@ -200,10 +269,11 @@ constexpr bool plane_length(int n) {
 // Planes a workgroup can hold: the lengths above, within a CU's 160 KB of LDS
 // less the block sums.
 constexpr size_t PLANE_LDS_MAX = 163840 - 512;
-constexpr size_t plane_lds_bytes(int ny, int nz, int elem) { return (size_t)ny * (nz / 2 + 1) * elem; }
+constexpr size_t plane_lds_bytes(int ny, int nz, int elem) { return (size_t)ny * plane_pitch(nz) * elem; }
 constexpr bool plane_fits(int ny, int nz, int elem) {
   return plane_length(ny) && plane_length(nz) && plane_lds_bytes(ny, nz, elem) <= PLANE_LDS_MAX;
 }
+void plane_groups(int ny, int nz, int* cols, int* rows);
 int plane_waves(int ny, int nz);
 
 inline bool plane_len_c0(int n) { return n == 32 || n == 48 || n == 64 || n == 96; }
@@ -211,10 +281,16 @@ inline int plane_class(int ny, int nz) { return plane_len_c0(ny) && plane_len_c0
 
 // y transforms of a plane for the lengths of class CLS.
 template <typename T, bool INV, int CLS>
-__device__ __forceinline__ void plane_cols_any(int ny, const cx<T>* src, cx<T>* dst, cx<T>* plane, int h,
+__device__ __forceinline__ void plane_cols_any(int ny, int nz, const cx<T>* src, cx<T>* dst, cx<T>* plane,
                                                const cx<T>* tw, int wave, int nwaves) {
-#define PL_C(NN) \
-  case NN: plane_cols<T, NN, INV>(src, dst, plane, h, tw, wave, nwaves); break;
+  const int h = nz / 2 + 1, pitch = plane_pitch(nz);
+#define PL_C(NN)                                                                            \
+  case NN:                                                                                  \
+    if (nz == NN && CLS == (NN == 128))                                                     \
+      plane_cols<T, NN, INV, NN / 2 + 1>(src, dst, plane, h, pitch, tw, wave, nwaves);      \
+    else                                                                                    \
+      plane_cols<T, NN, INV, 0>(src, dst, plane, h, pitch, tw, wave, nwaves);               \
+    break;
   if constexpr (CLS == 0) {
     switch (ny) {
       PL_PLANE_LENGTHS_C0(PL_C)
@@ -238,7 +314,7 @@ __device__ __forceinline__ void plane_body(const RowArgs<T>& a, int plane_id, bo
   const int h = a.n / 2 + 1;
   const long at = (long)plane_id * a.ny * h;
   if constexpr (row_from_half(OP)) {
-    if (on) plane_cols_any<T, true, CLS>(a.ny, a.in_c + at, nullptr, plane, h, a.tw_y, wave, nwaves);
+    if (on) plane_cols_any<T, true, CLS>(a.ny, a.n, a.in_c + at, nullptr, plane, a.tw_y, wave, nwaves);
     __syncthreads();
   }
   if (on) {
@@ -259,7 +335,7 @@ __device__ __forceinline__ void plane_body(const RowArgs<T>& a, int plane_id, bo
   }
   if constexpr (row_to_half(OP)) {
     __syncthreads();
-    if (on) plane_cols_any<T, false, CLS>(a.ny, nullptr, a.out_c + at, plane, h, a.tw_y, wave, nwaves);
+    if (on) plane_cols_any<T, false, CLS>(a.ny, a.n, nullptr, a.out_c + at, plane, a.tw_y, wave, nwaves);
   }
 }
 
@@ -276,6 +352,26 @@ __global__ void __launch_bounds__(PLANE_MAX_WAVES * 64) plane_kernel(RowArgs<T> 
   double acc[2] = {0.0, 0.0};
   plane_body<T, OP, CLS>(a, blockIdx.x, true, reinterpret_cast<cx<T>*>(plane_lds), threadIdx.x >> 6, blockDim.x >> 6, acc);
   if constexpr (row_has_sums(OP)) block_reduce_store<2>(acc, a.partials, blockIdx.x);
+}
+
+// Batched plane pass: a block takes G = PLANE_BATCH_WAVES / w planes of one
+// instance, w waves each (planes of short rows would leave most of a block
+// idle); work item: (instance, first plane, w, block index in the instance).
+constexpr int PLANE_BATCH_WAVES = 8;
+
+template <typename T, int OP, int CLS>
+__global__ void __launch_bounds__(PLANE_BATCH_WAVES * 64) plane_batch_kernel(const RowArgs<T>* __restrict__ args,
+                                                                            const int4* __restrict__ work) {
+  const int4 w = work[blockIdx.x];
+  const RowArgs<T> a = args[w.x];
+  if (a.skip && *a.skip != 0.0) return;
+  const int wave = threadIdx.x >> 6, slot = wave / w.z, planes = PLANE_BATCH_WAVES / w.z;
+  const int id = w.y + slot;
+  const bool on = slot < planes && id < a.nplanes;
+  cx<T>* plane = reinterpret_cast<cx<T>*>(plane_lds) + (on ? slot : 0) * a.ny * plane_pitch(a.n);
+  double acc[2] = {0.0, 0.0};
+  plane_body<T, OP, CLS>(a, id, on, plane, wave - slot * w.z, w.z, acc);
+  if constexpr (row_has_sums(OP)) block_reduce_store<2>(acc, a.partials, w.w);
 }
 
 }  // namespace pl
