@@ -258,46 +258,68 @@ __device__ __forceinline__ int out_pos(int t, int q, int m) {
   return (j - k) * R + k + m * Ns;
 }
 
-// Twiddle tables: tw[e] = exp(-2 pi i e / N), e in [0, N).
-template <class PL, int S, bool INV, typename T>
-__device__ __forceinline__ void stage_compute(cx<T>* v, int t, const cx<T>* __restrict__ tw) {
+// Twiddle tables: tw[e] = exp(-2 pi i e / N), e in [0, N).  A butterfly's
+// powers w^r, r = 1..R-1, of w = exp(-2 pi i k / (Ns R)) come from w^1, w^2,
+// w^4, w^8 of the table, the rest as products of at most three of them (a few
+// ulp, instead of one table load per power).
+template <class PL, int S>
+struct StageTw {
+  static constexpr int R = StageInfo<PL, S>::R;
+  static constexpr int LOADS = StageInfo<PL, S>::NS == 1 ? 0 : (R > 8 ? 4 : (R > 4 ? 3 : (R > 2 ? 2 : 1)));
+};
+// Load the table entries of stage S (LOADS per butterfly) into base[].
+template <class PL, int S, typename T>
+__device__ __forceinline__ void stage_twiddles(cx<T>* base, int t, const cx<T>* __restrict__ tw) {
   constexpr int R = StageInfo<PL, S>::R;
   constexpr int Ns = StageInfo<PL, S>::NS;
-  constexpr int Q = PL::W / R;
+  constexpr int L = StageTw<PL, S>::LOADS;
   constexpr int STEP = PL::N / (Ns * R);
+  if constexpr (L > 0) {
+#pragma unroll
+    for (int q = 0; q < PL::W / R; ++q) {
+      const int k = (t + PL::P * q) % Ns;
+#pragma unroll
+      for (int i = 0; i < L; ++i) base[q * L + i] = tw[(k << i) * STEP];
+    }
+  }
+}
+template <class PL, int S, bool INV, typename T>
+__device__ __forceinline__ void stage_butterflies(cx<T>* v, const cx<T>* base) {
+  constexpr int R = StageInfo<PL, S>::R;
+  constexpr int L = StageTw<PL, S>::LOADS;
+  constexpr int Q = PL::W / R;
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     cx<T>* b = v + q * R;
-    if constexpr (Ns > 1) {
-      int k = (t + PL::P * q) % Ns;
-      // powers w^r, r = 1..R-1, of w = exp(-2 pi i k / (Ns R)): w^1, w^2,
-      // w^4, w^8 from the table, the rest as products of at most three of
-      // them (a few ulp, instead of one table load per power)
+    if constexpr (L > 0) {
       cx<T> w[R];
-      w[1] = tw[k * STEP];
-      if constexpr (R > 2) w[2] = tw[2 * k * STEP];
-      if constexpr (R == 3) {
-      } else {
-        if constexpr (R > 3) w[3] = cmul(w[1], w[2]);
-        if constexpr (R > 4) {
-          w[4] = tw[4 * k * STEP];
-          w[5] = cmul(w[4], w[1]);
-        }
-        if constexpr (R > 6) {
-          w[6] = cmul(w[4], w[2]);
-          w[7] = cmul(w[4], w[3]);
-        }
-        if constexpr (R > 8) {
-          w[8] = tw[8 * k * STEP];
+      w[1] = base[q * L];
+      if constexpr (R > 2) w[2] = base[q * L + 1];
+      if constexpr (R > 3) w[3] = cmul(w[1], w[2]);
+      if constexpr (R > 4) {
+        w[4] = base[q * L + 2];
+        w[5] = cmul(w[4], w[1]);
+      }
+      if constexpr (R > 6) {
+        w[6] = cmul(w[4], w[2]);
+        w[7] = cmul(w[4], w[3]);
+      }
+      if constexpr (R > 8) {
+        w[8] = base[q * L + 3];
 #pragma unroll
-          for (int r = 9; r < R; ++r) w[r] = cmul(w[8], w[r - 8]);
-        }
+        for (int r = 9; r < R; ++r) w[r] = cmul(w[8], w[r - 8]);
       }
 #pragma unroll
       for (int r = 1; r < R; ++r) b[r] = INV ? cmulc(b[r], w[r]) : cmul(b[r], w[r]);
     }
     dft_r<R, INV>(b);
   }
+}
+template <class PL, int S, bool INV, typename T>
+__device__ __forceinline__ void stage_compute(cx<T>* v, int t, const cx<T>* __restrict__ tw) {
+  cx<T> base[StageTw<PL, S>::LOADS ? StageTw<PL, S>::LOADS * (PL::W / StageInfo<PL, S>::R) : 1];
+  stage_twiddles<PL, S>(base, t, tw);
+  stage_butterflies<PL, S, INV>(v, base);
 }
 
 // LDS accessor: element e of the transform lives at base[e * STRIDE + pad],

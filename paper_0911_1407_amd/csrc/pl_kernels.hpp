@@ -373,9 +373,8 @@ constexpr int col_tile(int P, int N, int elem_bytes, int threads, int lds_cap) {
   return b;
 }
 
-// V = 2 ("narrow", batched launches only): 128 threads and at most 32 KB,
-// for the small grids of a batch, whose short columns leave most lanes of a
-// default tile idle (a y pass of a 32^3 grid has 17 columns).
+// V = 2 ("narrow"): 128 threads and at most 32 KB, for batches of small grids
+// and for x passes of few columns (see x_tile).
 // V = 3 ("split"): the default tile, with the stage exchanges passing real
 // and imaginary parts through LDS one after the other (half the LDS, so
 // twice the blocks per CU when registers allow) and the second operand of
@@ -386,10 +385,13 @@ constexpr int col_tile(int P, int N, int elem_bytes, int threads, int lds_cap) {
 // the wide tile's row segments (512 bytes of FP64 columns at 256 points)
 // at two blocks per CU.  V = 6 ("extra wide split"): 1024 threads, split
 // exchanges in at most 128 KB (1 KB segments of FP64 at 256 points).
-constexpr int col_threads(int V) { return V == 1 || V == 5 ? 512 : (V == 2 ? 128 : (V == 4 || V == 6 ? 1024 : 256)); }
-constexpr int col_lds_cap(int V) {
-  return V == 1 || V == 6 ? 131072 : (V == 2 ? 32768 : (V == 4 ? 163840 : 65536));
+constexpr int col_threads(int V) {
+  return V == 1 || V == 5 ? 512 : (V == 2 ? 128 : (V == 4 || V == 6 ? 1024 : (V == 7 ? 64 : 256)));
 }
+constexpr int col_lds_cap(int V) {
+  return V == 1 || V == 6 ? 131072 : (V == 2 || V == 7 ? 32768 : (V == 4 ? 163840 : 65536));
+}
+// V = 7 ("one wave"): 64 threads, for the x passes of small grids (see x_tile).
 constexpr bool col_split(int V) { return V == 3 || V == 5 || V == 6; }
 
 template <typename T, int N, int V = 0>
@@ -946,7 +948,8 @@ struct BlockRowFft {
   using PL = Plan<N>;
   using Fwd = PL;
   using MAP = LdsMap<1, true>;
-  static constexpr bool PRELOAD_D = true, STREAM = true, GAUSS = true;
+  static constexpr int PRELOAD_D = PL::W;
+  static constexpr bool STREAM = true, GAUSS = true;
   int t;
   cx<T>* lds;
   const cx<T>* tw;
@@ -1037,17 +1040,14 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
 
   // ROW_HVP / ROW_LB_IN: the diagonal at the positions this thread
   // multiplies, loaded before the transforms so that its latency overlaps them
-  constexpr bool PRE_D = (OP == ROW_HVP || OP == ROW_LB_IN) && FX::PRELOAD_D;
-  T pre_dA[PRE_D ? W : 1], pre_dB[PRE_D ? W : 1];
-  if constexpr (PRE_D) {
+  // (FX::PRELOAD_D of them)
+  constexpr int PRE_D = OP == ROW_HVP || OP == ROW_LB_IN ? FX::PRELOAD_D : 0;
+  T pre_dA[PRE_D ? PRE_D : 1], pre_dB[PRE_D ? PRE_D : 1];
 #pragma unroll
-    for (int q = 0; q < W / RL; ++q)
-#pragma unroll
-      for (int m = 0; m < RL; ++m) {
-        const int e = active ? out_pos<PL, PL::NS - 1>(t, q, m) : 0;
-        pre_dA[q * RL + m] = diag_at<T>(a, rowA * N + e, nt_d);
-        pre_dB[q * RL + m] = diag_at<T>(a, rowB * N + e, nt_d);
-      }
+  for (int i = 0; i < PRE_D; ++i) {
+    const int e = active ? out_pos<PL, PL::NS - 1>(t, i / RL, i % RL) : 0;
+    pre_dA[i] = diag_at<T>(a, rowA * N + e, nt_d);
+    pre_dB[i] = diag_at<T>(a, rowB * N + e, nt_d);
   }
 
   if constexpr (OP == ROW_R2C || OP == ROW_GRAD_STEP) {
@@ -1116,7 +1116,7 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
 #pragma unroll
           for (int m = 0; m < RL; ++m) {
             T dA, dB;
-            if constexpr (PRE_D) {
+            if (q * RL + m < PRE_D) {
               dA = pre_dA[q * RL + m];
               dB = pre_dB[q * RL + m];
             } else {
@@ -1148,7 +1148,7 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
               acc[0] += a.lb_d1[rowA * N + e] * (double)va * va + a.lb_d1[rowB * N + e] * (double)vb * vb;
             }
             T dA, dB;
-            if constexpr (PRE_D) {
+            if (q * RL + m < PRE_D) {
               dA = pre_dA[q * RL + m];
               dB = pre_dB[q * RL + m];
             } else {

@@ -263,12 +263,29 @@ ColArgs<T> col_args(pl_plan* p, int axis, const cx<T>* in, cx<T>* out) {
   return a;
 }
 
+// Tile variant of an x pass whose schedule choice is v.  The default tile
+// (256 threads) leaves most of the 256 CUs without a workgroup on small grids
+// (9 workgroups at 32^3, 147 at 96^3), and their x passes are chains of
+// latencies: so a tile of one wave as long as every CU gets at most one, else
+// the narrow tile (128 threads) as long as every CU gets at most four.
+// Measured, us per Hessian product / CG iteration, default / narrow / one wave:
+// 32^3 16.2 / 15.2 / 14.9 and 24.1 / 22.7 / 22.2, 96^3 36.6 / 36.2 / 35.1 and
+// 50.9 / 50.6 / 50.3, 128^3 46.6 / 43.6 / 43.4 and 63.4 / 62.2 / 64.2; a 64^3
+// FP32 solve (264 workgroups of one wave) 9.5 / 9.2 / 9.9 ms.
+int x_tile(const pl_plan* p, int v) {
+  const int n = p->n[0];
+  if (v != 0 || n < 32 || n > 128) return v;
+  const long cols = (long)p->n[1] * p->g.h, per = n <= 48 ? 16 : 8;  // columns of a wave
+  if (cols <= 256 * per) return 7;
+  return cols <= 1024 * 2 * per ? 2 : 0;
+}
+
 template <typename T>
 hipError_t run_col(pl_plan* p, int axis, bool inverse, int op, const ColArgs<T>& a, int* nb) {
   int dummy;
   const int pi = sizeof(T) == 4 ? 1 : 0;
   const bool krylov = op == COL_CG_FIRST || op == COL_CG_LAST || op == COL_CG_INIT || op == COL_CG_STEP;
-  const int v = axis == 1 ? p->var[pi][V_Y] : p->var[pi][krylov ? V_XCG : V_XOP];
+  const int v = axis == 1 ? p->var[pi][V_Y] : x_tile(p, p->var[pi][krylov ? V_XCG : V_XOP]);
   const int nslabs = axis == 0 ? 1 : p->n[0];
   if (op == COL_PLAIN) return launch_col<T>(p->n[axis], inverse, op, a, nslabs, p->stream, nb ? nb : &dummy, v);
   ColArgs<T> b = a;  // the 1/lambda table this pass reads (TabKind)
@@ -344,9 +361,10 @@ bool use_plane(const pl_plan* p, int op) {
 // The y and z passes of an operator on the half spectrum buf (in place): y
 // inverse for row operations that start from half rows, the row operation,
 // y forward for those that end in half rows; as one plane pass where the
-// grid's planes allow it.  *nb: blocks that left partial sums.
+// grid's planes allow it.  *nb: blocks that left partial sums.  fin (separate
+// passes only): a finalize of those sums that rides on the y forward pass.
 template <typename T>
-int run_yz(pl_plan* p, int op, cx<T>* buf, RowArgs<T> ra, int* nb = nullptr) {
+int run_yz(pl_plan* p, int op, cx<T>* buf, RowArgs<T> ra, int* nb = nullptr, const FinArgs* fin = nullptr) {
   ra.in_c = buf;
   ra.out_c = buf;
   int dummy;
@@ -357,7 +375,12 @@ int run_yz(pl_plan* p, int op, cx<T>* buf, RowArgs<T> ra, int* nb = nullptr) {
   ColArgs<T> c = col_args<T>(p, 1, buf, buf);
   c.skip = ra.skip;
   if (row_from_half(op)) HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, c, nullptr));
-  HIPCHK(p, run_row<T>(p, op, ra, nb));
+  HIPCHK(p, run_row<T>(p, op, ra, nb ? nb : &dummy));
+  if (fin) {
+    c.fin_on = 1;
+    c.fin = *fin;
+    c.fin.nb = nb ? *nb : dummy;
+  }
   if (row_to_half(op)) HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, c, nullptr));
   return PL_OK;
 }
@@ -562,18 +585,12 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
         c.beta_part = part_in;
         c.beta_nb = nbx;
       } else {
-        ColArgs<T> cy = col_args<T>(p, 1, t, t);
-        cy.skip = skip;
-        HIPCHK(p, run_col<T>(p, 1, true, COL_PLAIN, cy, nullptr));
-        ra.in_c = t;
-        ra.out_c = t;
-        HIPCHK(p, run_row<T>(p, ROW_HVP, ra, &nbz));
         // the iteration's scalars, by an extra workgroup of the y pass
         // (which does not need them; the x pass does)
         const int kind = kOnePass ? FIN_CG_STEP : (k == 0 ? FIN_CG_ALPHA_FIRST : FIN_CG_ALPHA_K);
-        cy.fin_on = 1;
-        cy.fin = FinArgs{part_z, nbz, 2, kind, k, 1.0, p->scal, (double)max_cg, part_in, nbx, invN};
-        HIPCHK(p, run_col<T>(p, 1, false, COL_PLAIN, cy, nullptr));
+        const FinArgs fin{part_z, 0, 2, kind, k, 1.0, p->scal, (double)max_cg, part_in, nbx, invN};
+        rc = run_yz<T>(p, ROW_HVP, t, ra, &nbz, &fin);
+        if (rc) return rc;
       }
       if constexpr (kOnePass) {
         c.cg_p = pp;
@@ -3104,7 +3121,8 @@ namespace {
 // The x pass with the caller's table (run_col substitutes the prior's)
 hipError_t run_col_own_table(pl_plan* p, bool inverse, int op, const ColArgs<double>& a, int* nb) {
   int dummy;
-  return launch_col<double>(p->n[0], inverse, op, a, 1, p->stream, nb ? nb : &dummy, p->var[0][V_XOP]);
+  return launch_col<double>(p->n[0], inverse, op, a, 1, p->stream, nb ? nb : &dummy,
+                            x_tile(p, p->var[0][V_XOP]));
 }
 
 // out = B in for real fields: z r2c, y forward, the x pass's forward

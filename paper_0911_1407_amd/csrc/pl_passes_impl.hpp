@@ -73,6 +73,7 @@ static hipError_t row_launch_n(int op, const RowArgs<T>& a, hipStream_t st, int*
 #define PL_LENGTHS(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(512)
 
 #define PL_WIDE_LENGTHS(X) X(128) X(192) X(256) X(512)
+#define PL_NARROW_LENGTHS(X) X(32) X(48) X(64) X(96) X(128)
 
 template <>
 hipError_t launch_col<PL_T>(int N, bool inverse, int op, const ColArgs<PL_T>& a, int nslabs, hipStream_t st,
@@ -109,6 +110,17 @@ hipError_t launch_col<PL_T>(int N, bool inverse, int op, const ColArgs<PL_T>& a,
 #define PL_CASE(NN) \
   case NN: return col_launch_n<PL_T, NN, 6>(inverse, op, a, nslabs, st, nblocks);
       PL_WIDE_LENGTHS(PL_CASE)
+#undef PL_CASE
+      default: break;
+    }
+  }
+  if (variant == 2 || variant == 7) {
+    switch (N) {
+#define PL_CASE(NN)                                                                        \
+  case NN:                                                                                 \
+    return variant == 2 ? col_launch_n<PL_T, NN, 2>(inverse, op, a, nslabs, st, nblocks)   \
+                        : col_launch_n<PL_T, NN, 7>(inverse, op, a, nslabs, st, nblocks);
+      PL_NARROW_LENGTHS(PL_CASE)
 #undef PL_CASE
       default: break;
     }

@@ -143,25 +143,33 @@ __device__ __forceinline__ void wave_fft(cx<T>* v, int t, cx<T>* lds, const cx<T
   if constexpr (PL::P == 1) {
     fft_thread<PL, INV, LdsMap<1, false>>(v, t, lds, tw);
   } else {
+    // each stage's twiddles are asked for a stage ahead, so that the loads'
+    // latency overlaps the exchange (its scheduling fences would put them
+    // behind it)
+    constexpr int S2 = PL::NS > 2 ? 2 : 1;
+    cx<T> w1[StageTw<PL, 1>::LOADS * (PL::W / StageInfo<PL, 1>::R)];
+    cx<T> w2[StageTw<PL, S2>::LOADS * (PL::W / StageInfo<PL, S2>::R)];
+    stage_twiddles<PL, 1>(w1, t, tw);
     stage_compute<PL, 0, INV>(v, t, tw);
-    if constexpr (PL::NS > 1) {
-      wave_exchange<PL, 0, 1>(v, t, lds, off);
-      stage_compute<PL, 1, INV>(v, t, tw);
-    }
+    wave_exchange<PL, 0, 1>(v, t, lds, off);
+    if constexpr (PL::NS > 2) stage_twiddles<PL, 2>(w2, t, tw);
+    stage_butterflies<PL, 1, INV>(v, w1);
     if constexpr (PL::NS > 2) {
       wave_exchange<PL, 1, 2>(v, t, lds, off);
-      stage_compute<PL, 2, INV>(v, t, tw);
+      stage_butterflies<PL, 2, INV>(v, w2);
     }
   }
 }
 
-template <typename T, int N>
+template <typename T, int N, bool PRE>
 struct WaveRowFft {
   using PL = Plan<N>;
   using Fwd = RevPlan<PL>;  // takes over the inverse transform's slots
-  // two diagonal values per held element: beyond 8 FP64 elements they would
-  // not leave registers for the twiddles
-  static constexpr bool PRELOAD_D = sizeof(T) == 4 || PL::W <= 8, STREAM = false;
+  // elements whose diagonal is loaded ahead (two values each): none in FP64
+  // beside the longer bodies of class 1, which would spill (3 registers too many
+  // took the 128 x 128 plane from 22 to 31 us)
+  static constexpr int PRELOAD_D = PRE ? PL::W : 0;
+  static constexpr bool STREAM = false;
   // the Gaussian model keeps the row passes: its log1p beside the exp left
   // the plane's gradient kernels 172-468 spilled registers
   static constexpr bool GAUSS = false;
@@ -229,7 +237,7 @@ __device__ __forceinline__ void plane_cols(const cx<T>* __restrict__ src, cx<T>*
 }
 
 // z transforms and pointwise work of a plane's row pairs.
-template <typename T, int N, int OP>
+template <typename T, int N, int OP, bool PRE>
 __device__ __forceinline__ void plane_rows(const RowArgs<T>& a, cx<T>* plane, long row0, int wave, int nwaves,
                                            double (&acc)[2]) {
   using PL = Plan<N>;
@@ -241,7 +249,7 @@ __device__ __forceinline__ void plane_rows(const RowArgs<T>& a, cx<T>* plane, lo
     const int t = per_round(lane % P) & (P - 1);
     const int u = min(g * U + ul, pairs - 1);
     cx<T>* rows = plane + 2 * u * H;
-    const WaveRowFft<T, N> fx{t, rows, a.tw};
+    const WaveRowFft<T, N, PRE> fx{t, rows, a.tw};
     const long rowA = row0 + 2 * u;
     double part[2] = {0.0, 0.0};
     row_core<T, N, OP>(a, fx, t, true, true, rowA, rowA + 1, rows, rows + H, rows, rows + H, part);
@@ -311,6 +319,7 @@ __device__ __forceinline__ void plane_cols_any(int ny, int nz, const cx<T>* src,
 template <typename T, int OP, int CLS>
 __device__ __forceinline__ void plane_body(const RowArgs<T>& a, int plane_id, bool on, cx<T>* plane, int wave,
                                            int nwaves, double (&acc)[2]) {
+  constexpr bool PRE = sizeof(T) == 4 || CLS == 0;
   const int h = a.n / 2 + 1;
   const long at = (long)plane_id * a.ny * h;
   if constexpr (row_from_half(OP)) {
@@ -319,7 +328,7 @@ __device__ __forceinline__ void plane_body(const RowArgs<T>& a, int plane_id, bo
   }
   if (on) {
 #define PL_C(NN) \
-  case NN: plane_rows<T, NN, OP>(a, plane, (long)plane_id * a.ny, wave, nwaves, acc); break;
+  case NN: plane_rows<T, NN, OP, PRE>(a, plane, (long)plane_id * a.ny, wave, nwaves, acc); break;
     if constexpr (CLS == 0) {
       switch (a.n) {
         PL_PLANE_LENGTHS_C0(PL_C)
@@ -341,13 +350,14 @@ __device__ __forceinline__ void plane_body(const RowArgs<T>& a, int plane_id, bo
 
 // Waves of a single-grid plane pass: as many as there are wave-sized groups
 // of columns or row pairs, at most 10 (an FP64 128 x 128 plane: 9 groups of
-// columns, 8 of pairs; three waves per SIMD leave 168 registers each).
+// columns, 8 of pairs; three waves per SIMD leave 168 registers each).  Planes
+// of class 0 have at most 7 groups of either.
 constexpr int PLANE_MAX_WAVES = 10;
 
 extern __shared__ __align__(16) char plane_lds[];
 
 template <typename T, int OP, int CLS>
-__global__ void __launch_bounds__(PLANE_MAX_WAVES * 64) plane_kernel(RowArgs<T> a) {
+__global__ void __launch_bounds__((CLS == 0 ? 8 : PLANE_MAX_WAVES) * 64) plane_kernel(RowArgs<T> a) {
   if (a.skip && *a.skip != 0.0) return;  // Krylov iteration after convergence
   double acc[2] = {0.0, 0.0};
   plane_body<T, OP, CLS>(a, blockIdx.x, true, reinterpret_cast<cx<T>*>(plane_lds), threadIdx.x >> 6, blockDim.x >> 6, acc);
