@@ -2049,42 +2049,40 @@ void col_work(const std::vector<pl_plan*>& plans, const std::vector<int>& var, B
   join_classes(w, cls);
 }
 
-// Waves that share a plane in a batched block of PLANE_BATCH_WAVES: the split
-// that finishes the most planes per unit of time, a plane taking the rounds of
-// its columns (twice, both y transforms) and of its row pairs.  (FP32 64 x 64:
-// two planes of 4 waves, 5 rounds, before one of 5 waves, 3 rounds.)
-int plane_batch_waves(int ny, int nz) {
-  int cols, rows, best = 1;
-  plane_groups(ny, nz, &cols, &rows);
-  double rate = 0.0;
-  for (int w = 1; w <= PLANE_BATCH_WAVES; ++w) {
-    const int rounds = 2 * ((cols + w - 1) / w) + (rows + w - 1) / w;
-    const double r = (double)(PLANE_BATCH_WAVES / w) / rounds;
-    if (r > rate * 1.0001) {
-      rate = r;
-      best = w;
-    }
-  }
-  return best;
-}
-
-// Plane pass over all instances.
+// Plane pass over all instances: blocks of 4 or 8 waves holding one or more
+// planes each.  Up to 256 planes (one per CU) what counts is how long one takes:
+// a block each, at the most waves a plane can use.  Beyond, 4 waves per block
+// where three such blocks share a CU's LDS (small planes, FP32 up to 96 x 96),
+// else 8; planes that use fewer waves share a block.  Measured: 16 mixed
+// instances of 32^3-96^3, 8 waves throughout 36 us per plane pass and 66.5 ms,
+// with this 26.6 us and 59.6 ms; 4 of 32 x 32 x 64 22.3 and 15.8 ms.
 template <typename T>
 void plane_work(const std::vector<pl_plan*>& plans, BWork& w, const std::vector<int>* subset = nullptr) {
   std::vector<int4> cls[BATCH_CLASSES];
   w.nb.assign(plans.size(), 0);
   for (int c = 0; c < BATCH_CLASSES; ++c) w.threads[c] = w.lds[c] = 0;
+  auto in = [&](size_t i) { return !subset || (*subset)[i]; };
+  long planes = 0;
+  size_t largest = 0;
+  for (size_t i = 0; i < plans.size(); ++i)
+    if (in(i)) {
+      planes += plans[i]->n[0];
+      largest = std::max(largest, plane_lds_bytes(plans[i]->n[1], plans[i]->n[2], (int)sizeof(cx<T>)));
+    }
+  const bool few = planes <= 256;
+  const int block = few || 3 * largest > PLANE_LDS_MAX ? PLANE_BATCH_WAVES : PLANE_BATCH_WAVES / 2;
   for (size_t i = 0; i < plans.size(); ++i) {
-    if (subset && !(*subset)[i]) continue;
+    if (!in(i)) continue;
     const pl_plan* p = plans[i];
     const int c = plane_class(p->n[1], p->n[2]);
     const size_t one = plane_lds_bytes(p->n[1], p->n[2], (int)sizeof(cx<T>));
-    int waves = plane_batch_waves(p->n[1], p->n[2]);
-    while ((PLANE_BATCH_WAVES / waves) * one > PLANE_LDS_MAX) ++waves;  // (one plane always fits)
-    const int per = PLANE_BATCH_WAVES / waves;
-    const int nb = (p->n[0] + per - 1) / per;
-    for (int t = 0; t < nb; ++t) cls[c].push_back(make_int4((int)i, t * per, waves, t));
-    w.nb[i] = nb;
+    int waves = std::min(block, plane_waves(p->n[1], p->n[2]));
+    if (!few && block == 8 && waves == 5) waves = 4;  // two planes of 4 waves, not one of 5
+    int per = few ? 1 : block / waves;
+    while (per * one > std::max(largest, PLANE_LDS_MAX / 2)) --per;  // (at least one plane fits)
+    for (int t = 0; t < p->n[0]; t += per) cls[c].push_back(make_int4((int)i, t, waves | per << 8, 0));
+    w.nb[i] = p->n[0];  // sums: a record per plane
+    w.threads[c] = 64 * block;
     w.lds[c] = std::max(w.lds[c], (int)(per * one));
   }
   join_classes(w, cls);
@@ -2249,7 +2247,8 @@ hipError_t bplane(pl_batch* b, int op, const RowArgs<T>* args, int wid) {
   const int count[2] = {w.split, (int)w.items.size() - w.split};
   for (int c = 0, first = 0; c < BATCH_CLASSES; first += count[c], ++c) {
     if (count[c] == 0) continue;
-    hipError_t e = launch_plane_batch<T>(op, c, args, work_dev(b, wid) + first, count[c], w.lds[c], b->stream);
+    hipError_t e = launch_plane_batch<T>(op, c, args, work_dev(b, wid) + first, count[c], w.threads[c], w.lds[c],
+                                         b->stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -2960,8 +2959,17 @@ int pl_batch_create(pl_batch** out, int n_inst, const int32_t* n, const double* 
   build_work(b);
   for (int i = 0; i < W_COUNT; ++i) b->work[i].cap = b->work[i].items.size();
   b->work[W_XC].cap = std::max(b->work[W_X64].cap, b->work[W_X32].cap);
-  b->work[W_PC].cap = std::max(b->work[W_P64].cap, b->work[W_P32].cap);
-  for (int t = 0; t < 2; ++t) b->vcol[t].assign(n_inst, 0);
+  // (a subset of few planes takes a block for each)
+  b->work[W_PC].cap = 0;
+  for (const pl_plan* p : b->plans) b->work[W_PC].cap += p->n[0];
+  long x_blocks = 0;
+  for (const pl_plan* p : b->plans) {
+    const int B = batch_shape<double>(p->n[0], 0).B;
+    x_blocks += (p->n[1] * p->g.h + B - 1) / B;
+  }
+  // the narrow tile while the default one leaves at most six workgroups per CU
+  // (16 mixed instances of 32^3-96^3, 1100 workgroups: 66.9 and 66.4 ms)
+  for (int t = 0; t < 2; ++t) b->vcol[t].assign(n_inst, x_blocks <= 1536 ? 2 : 0);
   build_work(b);
   b->blob_bytes = batch_layout(b);
   b->ws_bytes = b->plans_bytes + b->blob_bytes;

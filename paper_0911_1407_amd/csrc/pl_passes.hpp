@@ -27,7 +27,7 @@ template <typename T>
 hipError_t launch_plane(int op, const RowArgs<T>& a, hipStream_t st, int* nblocks);
 // The batched form over a work list of one length class (plane_class).
 template <typename T>
-hipError_t launch_plane_batch(int op, int cls, const RowArgs<T>* args, const int4* work, int nblocks, int lds_bytes,
-                              hipStream_t st);
+hipError_t launch_plane_batch(int op, int cls, const RowArgs<T>* args, const int4* work, int nblocks, int threads,
+                              int lds_bytes, hipStream_t st);
 
 }  // namespace pl

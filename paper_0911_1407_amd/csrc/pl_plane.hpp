@@ -364,9 +364,11 @@ __global__ void __launch_bounds__((CLS == 0 ? 8 : PLANE_MAX_WAVES) * 64) plane_k
   if constexpr (row_has_sums(OP)) block_reduce_store<2>(acc, a.partials, blockIdx.x);
 }
 
-// Batched plane pass: a block takes G = PLANE_BATCH_WAVES / w planes of one
-// instance, w waves each (planes of short rows would leave most of a block
-// idle); work item: (instance, first plane, w, block index in the instance).
+// Batched plane pass: a block takes up to `per` planes of one instance, w
+// waves each (planes of short rows would leave most of a block idle); work
+// item: (instance, first plane, w | per << 8, -).  The sums have a record per
+// plane, however the planes are split: a block's go to its first plane's, zeros
+// to the others'.
 constexpr int PLANE_BATCH_WAVES = 8;
 
 template <typename T, int OP, int CLS>
@@ -375,13 +377,17 @@ __global__ void __launch_bounds__(PLANE_BATCH_WAVES * 64) plane_batch_kernel(con
   const int4 w = work[blockIdx.x];
   const RowArgs<T> a = args[w.x];
   if (a.skip && *a.skip != 0.0) return;
-  const int wave = threadIdx.x >> 6, slot = wave / w.z, planes = PLANE_BATCH_WAVES / w.z;
+  const int waves = w.z & 255, wave = threadIdx.x >> 6, slot = wave / waves;
   const int id = w.y + slot;
-  const bool on = slot < planes && id < a.nplanes;
+  const bool on = slot < (w.z >> 8) && id < a.nplanes;
   cx<T>* plane = reinterpret_cast<cx<T>*>(plane_lds) + (on ? slot : 0) * a.ny * plane_pitch(a.n);
   double acc[2] = {0.0, 0.0};
-  plane_body<T, OP, CLS>(a, id, on, plane, wave - slot * w.z, w.z, acc);
-  if constexpr (row_has_sums(OP)) block_reduce_store<2>(acc, a.partials, w.w);
+  plane_body<T, OP, CLS>(a, id, on, plane, wave - slot * waves, waves, acc);
+  if constexpr (row_has_sums(OP)) {
+    block_reduce_store<2>(acc, a.partials, w.y);
+    const int others = min(w.z >> 8, a.nplanes - w.y) - 1;
+    if ((int)threadIdx.x < 2 * others) a.partials[2 * (w.y + 1) + threadIdx.x] = 0.0;
+  }
 }
 
 }  // namespace pl

@@ -38,9 +38,9 @@ hipError_t launch_plane<PL_T>(int op, const RowArgs<PL_T>& a, hipStream_t st, in
 }
 
 template <int CLS>
-static hipError_t launch_plane_batch_cls(int op, const RowArgs<PL_T>* args, const int4* work, int nblocks, int lds,
-                                         hipStream_t st) {
-  const dim3 grid(nblocks), block(64 * PLANE_BATCH_WAVES);
+static hipError_t launch_plane_batch_cls(int op, const RowArgs<PL_T>* args, const int4* work, int nblocks, int threads,
+                                         int lds, hipStream_t st) {
+  const dim3 grid(nblocks), block(threads);
   switch (op) {
     case ROW_C2R: hipLaunchKernelGGL((plane_batch_kernel<PL_T, ROW_C2R, CLS>), grid, block, lds, st, args, work); break;
     case ROW_HVP: hipLaunchKernelGGL((plane_batch_kernel<PL_T, ROW_HVP, CLS>), grid, block, lds, st, args, work); break;
@@ -57,10 +57,10 @@ static hipError_t launch_plane_batch_cls(int op, const RowArgs<PL_T>* args, cons
 
 template <>
 hipError_t launch_plane_batch<PL_T>(int op, int cls, const RowArgs<PL_T>* args, const int4* work, int nblocks,
-                                    int lds_bytes, hipStream_t st) {
-  if (nblocks < 1 || lds_bytes < 0 || (size_t)lds_bytes > PLANE_LDS_MAX) return hipErrorInvalidValue;
-  return cls == 0 ? launch_plane_batch_cls<0>(op, args, work, nblocks, lds_bytes, st)
-                  : launch_plane_batch_cls<1>(op, args, work, nblocks, lds_bytes, st);
+                                    int threads, int lds_bytes, hipStream_t st) {
+  if (nblocks < 1 || threads < 64 || threads > 64 * PLANE_BATCH_WAVES || threads % 64 || lds_bytes < 0 || (size_t)lds_bytes > PLANE_LDS_MAX) return hipErrorInvalidValue;
+  return cls == 0 ? launch_plane_batch_cls<0>(op, args, work, nblocks, threads, lds_bytes, st)
+                  : launch_plane_batch_cls<1>(op, args, work, nblocks, threads, lds_bytes, st);
 }
 
 }  // namespace pl
