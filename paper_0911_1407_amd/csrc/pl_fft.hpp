@@ -134,6 +134,26 @@ __device__ __forceinline__ void dft8(cx<T>* v) {
   v[7] = e3 - t3;
 }
 
+// 12 = 3 x 4, coprime: with n = 4 n1 + 3 n2 and k = 4 k1 + 9 k2 (mod 12) the
+// product n k is 4 n1 k1 + 3 n2 k2 (mod 12), so the DFT is one over n2 (length
+// 4) and one over n1 (length 3) with no twiddles between (Good 1958).
+template <bool INV, typename T>
+__device__ __forceinline__ void dft12(cx<T>* v) {
+  cx<T> f[3][4];
+#pragma unroll
+  for (int n1 = 0; n1 < 3; ++n1) {
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) f[n1][n2] = v[(4 * n1 + 3 * n2) % 12];
+    dft4<INV>(f[n1][0], f[n1][1], f[n1][2], f[n1][3]);
+  }
+#pragma unroll
+  for (int k2 = 0; k2 < 4; ++k2) {
+    dft3<INV>(f[0][k2], f[1][k2], f[2][k2]);
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) v[(4 * k1 + 9 * k2) % 12] = f[k1][k2];
+  }
+}
+
 // w16^e for e = 0..9 (forward sign), as (cos, -sin) pairs; inverse conjugates
 template <bool INV, typename T>
 __device__ __forceinline__ cx<T> w16(int e) {
@@ -189,13 +209,16 @@ __device__ __forceinline__ void dft_r(cx<T>* v) {
   else if constexpr (R == 4) dft4<INV>(v[0], v[1], v[2], v[3]);
   else if constexpr (R == 6) dft6<INV>(v);
   else if constexpr (R == 8) dft8<INV>(v);
+  else if constexpr (R == 12) dft12<INV>(v);
   else if constexpr (R == 16) dft16<INV>(v);
   else static_assert(R == 2, "unsupported radix");
 }
 
 // ---------------------------------------------------------------------------
 // Radix plans per transform length: radices R_0..R_{S-1} and threads P per
-// transform (each thread holds W = N/P values; every radix divides W).
+// transform (each thread holds W = N/P values; every radix divides W).  W is at
+// most 16: with 24 values per thread (24 = 8 3 and 192 = 8 8 3 on one and eight
+// threads) the registers left 6 waves per CU and spilled in the plane passes.
 // ---------------------------------------------------------------------------
 
 template <int N>
@@ -209,13 +232,13 @@ struct Plan;
 PL_PLAN(8, 1, 1, 8, 1, 1)
 PL_PLAN(12, 1, 2, 4, 3, 1)
 PL_PLAN(16, 1, 1, 16, 1, 1)
-PL_PLAN(24, 1, 2, 8, 3, 1)
+PL_PLAN(24, 2, 2, 4, 6, 1)
 PL_PLAN(32, 4, 2, 8, 4, 1)
 PL_PLAN(48, 4, 3, 4, 4, 3)
 PL_PLAN(64, 8, 2, 8, 8, 1)
 PL_PLAN(96, 8, 3, 4, 4, 6)
 PL_PLAN(128, 8, 2, 16, 8, 1)
-PL_PLAN(192, 8, 3, 8, 8, 3)
+PL_PLAN(192, 16, 3, 4, 4, 12)
 PL_PLAN(256, 16, 2, 16, 16, 1)
 PL_PLAN(512, 32, 3, 8, 8, 8)
 #undef PL_PLAN

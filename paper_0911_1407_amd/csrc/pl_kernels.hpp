@@ -1142,11 +1142,14 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
             const int e = out_pos<PL, PL::NS - 1>(t, q, m);
             cx<T> z = v[q * RL + m];
             const T va = z.x * a.scale, vb = z.y * a.scale;
+            // (loads outside the branch: one per element would wait for its own)
+            const T d1A = a.lb_d1[rowA * N + e], d1B = a.lb_d1[rowB * N + e];
             if (valid) {
               a.out_r[rowA * N + e] = va;
               a.out_r[rowB * N + e] = vb;
-              acc[0] += a.lb_d1[rowA * N + e] * (double)va * va + a.lb_d1[rowB * N + e] * (double)vb * vb;
             }
+            const double sum = (double)d1A * va * va + (double)d1B * vb * vb;
+            acc[0] += valid ? sum : 0.0;
             T dA, dB;
             if (q * RL + m < PRE_D) {
               dA = pre_dA[q * RL + m];
@@ -1165,16 +1168,10 @@ __device__ __forceinline__ void row_core(const RowArgs<T>& a, const FX& fx, cons
           for (int m = 0; m < RL; ++m) {
             const int e = out_pos<PL, PL::NS - 1>(t, q, m);
             cx<T> z = v[q * RL + m];
-            T o[2] = {T(0), T(0)};
-            if (valid) {
-#pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                const long i = (h ? rowB : rowA) * N + e;
-                const T g = (h ? z.y : z.x) * a.scale;
-                o[h] = (T)(a.d[i] * g + a.lb_d1[i] * a.lb_q[i]);
-              }
-            }
-            v[q * RL + m] = {o[0], o[1]};
+            const long iA = rowA * N + e, iB = rowB * N + e;
+            const T oA = a.d[iA] * (z.x * a.scale) + a.lb_d1[iA] * a.lb_q[iA];
+            const T oB = a.d[iB] * (z.y * a.scale) + a.lb_d1[iB] * a.lb_q[iB];
+            v[q * RL + m] = {valid ? oA : T(0), valid ? oB : T(0)};
             fx.chunk(q * RL + m);
           }
       } else {  // ROW_GRAD (double only)

@@ -355,6 +355,8 @@ int read_scalars(pl_plan* p) {
 template <typename T>
 bool use_plane(const pl_plan* p, int op) {
   if ((op == ROW_GRAD || op == ROW_GRAD_STEP) && p->model == MODEL_GAUSSIAN) return false;
+  // (its two diagonals spilled registers beside the longer bodies of class 1)
+  if (op == ROW_LB_IN && plane_class(p->n[1], p->n[2]) != 0) return false;
   return plane_fits(p->n[1], p->n[2], (int)sizeof(cx<T>));
 }
 

@@ -8,6 +8,14 @@
 // Small grids gain launches too: what bounds a 32^3 pass is its launch
 // (4.4 us), not its 0.3 MB.
 //
+// What bounds it: a plane runs on one CU, so a grid of fewer planes than CUs by
+// that CU's LDS and VALU in turn (96 x 96 FP64: 17500 LDS and 11000 VALU cycles
+// of 40000), a batch by how many planes a CU holds.  Measured, us per Hessian
+// product before (five passes) and now: 24^3 28.1 / 16.8, 32^3 22.6 / 14.9, 64^3
+// 25.9 / 18.3, 96^3 45.6 / 35, 128^3 59.5 / 43.8, 128^3 FP32 47.8 / 33.5,
+// 192^3 FP32 109 / 68, 64 x 192 x 96 51.5 / 48.4; 16 planes of 128 x 128 31.6 /
+// 28.5, the narrowest gain found, so every plane that fits is taken.
+//
 // Work split: a wave owns 64 / P whole transforms (P threads each, P divides
 // 64 for every length), so the exchanges between radix stages stay inside one
 // wave and need no workgroup barrier: LDS operations of a wave complete in
@@ -47,7 +55,7 @@ constexpr int log2_of(int r) { return r <= 1 ? 0 : 1 + log2_of(r / 2); }
 // lanes a radix apart meet different LDS banks.
 template <int N>
 struct RowPad {
-  static constexpr int SHIFT = Plan<N>::R0 >= 16 ? 4 : 3;
+  static constexpr int SHIFT = Plan<N>::R0 >= 16 || N == 192 ? 4 : 3;  // (192: so that 96 x 192 FP64 fits)
   static constexpr int LEN = Plan<N>::P == 1 ? N : N + (N >> SHIFT);
   static constexpr int off(int e) { return e + (e >> SHIFT); }
 };
@@ -56,11 +64,13 @@ struct RowPad {
 // banks for the lanes that read a column together.
 constexpr int plane_pitch(int nz) {
   switch (nz) {
+    case 24: return 14;
     case 32: return 18;
     case 48: return 27;
     case 64: return 36;
     case 96: return 54;
     case 128: return 68;
+    case 192: return 102;
     case 256: return 136;
     default: return nz / 2 + 1;
   }
@@ -80,7 +90,7 @@ constexpr int pos_out(int t, int q, int m) {
 // Whether OFF(position of slot (q, m)) is a part of the thread's plus a part of
 // the slot's, for every thread: then an exchange costs one address per thread
 // and the slots are instruction offsets.  (Not so where a radix of 3 or 6 meets
-// the padding: the first exchange of the reversed 48 and 96 plans.)
+// the padding: the first exchange of the reversed 24, 48, 96 and 192 plans.)
 template <class OFF, class PL, int S, bool OUT>
 constexpr bool splits() {
   constexpr int R = StageInfo<PL, S>::R;
@@ -265,7 +275,7 @@ __device__ __forceinline__ void plane_rows(const RowArgs<T>& a, cx<T>* plane, lo
 // the bodies of 16 and more values per thread (FP64: 156 registers) would hold
 // the planes of the shorter lengths (128) to their occupancy.
 #define PL_PLANE_LENGTHS_C0(X) X(32) X(48) X(64) X(96)
-#define PL_PLANE_LENGTHS(X) X(8) X(12) X(16) X(32) X(48) X(64) X(96) X(128) X(256)
+#define PL_PLANE_LENGTHS(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256)
 constexpr bool plane_length(int n) {
   switch (n) {
 #define PL_C(NN) case NN: return true;

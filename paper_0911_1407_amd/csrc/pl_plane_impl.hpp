@@ -18,7 +18,13 @@ static hipError_t launch_plane_cls(int op, const RowArgs<PL_T>& a, dim3 grid, di
     case ROW_C2R_GRADLIK:
       hipLaunchKernelGGL((plane_kernel<PL_T, ROW_C2R_GRADLIK, CLS>), grid, block, lds, st, a);
       break;
-    case ROW_LB_IN: hipLaunchKernelGGL((plane_kernel<PL_T, ROW_LB_IN, CLS>), grid, block, lds, st, a); break;
+    case ROW_LB_IN:
+      if constexpr (CLS == 0) {
+        hipLaunchKernelGGL((plane_kernel<PL_T, ROW_LB_IN, CLS>), grid, block, lds, st, a);
+        break;
+      } else {
+        return hipErrorInvalidValue;
+      }
     case ROW_LB_OUT: hipLaunchKernelGGL((plane_kernel<PL_T, ROW_LB_OUT, CLS>), grid, block, lds, st, a); break;
 #endif
     default: return hipErrorInvalidValue;

@@ -22,7 +22,8 @@ GRIDS = [
     (8, 8, 256), (8, 256, 8),               # the longest lengths beside the shortest
     (8, 128, 128), (12, 256, 64),           # the largest FP64 planes
     (8, 256, 128), (8, 128, 256),           # FP32 planes whose FP64 ones take the passes
-    (8, 256, 256), (8, 24, 32), (8, 96, 192),  # separate passes in both precisions
+    (8, 24, 192), (8, 192, 24), (8, 96, 192),  # lengths with radix 6 and 12 stages
+    (8, 192, 192), (8, 256, 256),  # FP32 planes only; separate passes in both precisions
 ]
 
 
