@@ -382,7 +382,7 @@ __global__ void __launch_bounds__((CLS == 0 ? 8 : PLANE_MAX_WAVES) * 64) plane_k
 constexpr int PLANE_BATCH_WAVES = 8;
 
 template <typename T, int OP, int CLS>
-__global__ void __launch_bounds__(PLANE_BATCH_WAVES * 64) plane_batch_kernel(const RowArgs<T>* __restrict__ args,
+__global__ void __launch_bounds__(PLANE_BATCH_WAVES * 64) row_batch_kernel(const RowArgs<T>* __restrict__ args,
                                                                             const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
   const RowArgs<T> a = args[w.x];

@@ -48,12 +48,12 @@ static hipError_t launch_plane_batch_cls(int op, const RowArgs<PL_T>* args, cons
                                          int lds, hipStream_t st) {
   const dim3 grid(nblocks), block(threads);
   switch (op) {
-    case ROW_C2R: hipLaunchKernelGGL((plane_batch_kernel<PL_T, ROW_C2R, CLS>), grid, block, lds, st, args, work); break;
-    case ROW_HVP: hipLaunchKernelGGL((plane_batch_kernel<PL_T, ROW_HVP, CLS>), grid, block, lds, st, args, work); break;
+    case ROW_R2C: hipLaunchKernelGGL((row_batch_kernel<PL_T, ROW_R2C, CLS>), grid, block, lds, st, args, work); break;
+    case ROW_C2R: hipLaunchKernelGGL((row_batch_kernel<PL_T, ROW_C2R, CLS>), grid, block, lds, st, args, work); break;
+    case ROW_HVP: hipLaunchKernelGGL((row_batch_kernel<PL_T, ROW_HVP, CLS>), grid, block, lds, st, args, work); break;
 #if PL_T_IS_DOUBLE
-    case ROW_R2C: hipLaunchKernelGGL((plane_batch_kernel<PL_T, ROW_R2C, CLS>), grid, block, lds, st, args, work); break;
     case ROW_GRAD:
-      hipLaunchKernelGGL((plane_batch_kernel<PL_T, ROW_GRAD, CLS>), grid, block, lds, st, args, work);
+      hipLaunchKernelGGL((row_batch_kernel<PL_T, ROW_GRAD, CLS>), grid, block, lds, st, args, work);
       break;
 #endif
     default: return hipErrorInvalidValue;
