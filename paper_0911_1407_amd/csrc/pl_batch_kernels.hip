@@ -13,7 +13,7 @@ __global__ void __launch_bounds__(BATCH_THREADS) col_batch_kernel(const ColArgs<
   cx<T>* lds_all = reinterpret_cast<cx<T>*>(batch_lds);
   const int4 w = work[blockIdx.x];
   const ColArgs<T> a = args[w.x];
-  if (a.skip && *a.skip != 0.0) return;
+  if (block_skips(a.skip)) return;
 #define PL_C(NN)                                                      \
   case NN:                                                            \
     if (a.variant == 2)                                               \

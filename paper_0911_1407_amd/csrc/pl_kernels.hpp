@@ -97,6 +97,20 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[K], double* __res
   }
 }
 
+// Whether a queued Krylov iteration is to be left out (*skip set), as one
+// lane reads it for its whole workgroup: workgroup 0 of the launch, or one
+// riding on it, may be storing the flag meanwhile, and waves that read it for
+// themselves could part, some leaving and the others going on with sums that
+// the leavers never stored.  Either reading is right for a whole workgroup
+// (one that goes on finds the same end from the same sums).
+__device__ __forceinline__ bool block_skips(const double* skip) {
+  if (!skip) return false;
+  __shared__ int off;
+  if (threadIdx.x == 0) off = *skip != 0.0;
+  __syncthreads();
+  return off != 0;
+}
+
 // Spectral bookkeeping for the half spectrum [nx][ny][h], h = nz/2 + 1.
 struct Grid {
   int nx, ny, nz, h;
@@ -194,7 +208,8 @@ __device__ __forceinline__ bool cg_scalars(double* scal, double delta, double ga
   if (STORE) {
     if (k == 0) {
       scal[SC_RR0] = rr;
-      scal[SC_TOL2] = tol2;
+      // (a given tolerance stays untouched: other workgroups read it)
+      if (tol_rel2 > 0.0) scal[SC_TOL2] = tol2;
     }
     scal[SC_ITS] = (double)k;
     scal[SC_RR] = rr;
@@ -247,7 +262,7 @@ __device__ __forceinline__ bool cg_alpha(double* scal, bool first, double pi, do
     const double tol2 = tol_rel2 > 0.0 ? tol_rel2 * rr : scal[SC_TOL2];
     end = rr <= tol2;  // converged at the start: x stays 0
     if (STORE) {
-      scal[SC_TOL2] = tol2;
+      if (tol_rel2 > 0.0) scal[SC_TOL2] = tol2;
       scal[SC_RR0] = scal[SC_RR] = rr;
       scal[cg_rz_slot(0)] = gamma;
       scal[SC_ITS] = 0.0;
@@ -490,13 +505,13 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
     // Krylov prologue on the x pass of a half spectrum (columns = (ky, kz)):
     //   p = M^-1 r + beta p_old (in place), partial sum of p^H Lambda^-1 p;
     // then the inverse transform of p.
-    const double beta = a.scal[SC_BETA], dbar = a.scal[SC_DBAR];
+    const double dbar = a.scal[SC_DBAR];
     const int kz = col_kz;
     const double hw = herm_w(kz, a.g);
     double acc[1] = {0.0};
     cx<T>* pio = const_cast<cx<T>*>(a.in);
     {
-      double beta_k = beta;
+      double beta_k = 0.0;
       int cg_k = a.cg_k;
       const double* beta_part = a.beta_part;
       if constexpr (BATCHED) {
@@ -524,6 +539,8 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
           if (done) sc[SC_DONE] = 1.0;
         }
         if (done) return;  // the whole workgroup (every one decides alike)
+      } else {
+        beta_k = a.scal[SC_BETA];
       }
 #pragma unroll
       for (int q = 0; q < W / R0; ++q)
@@ -786,7 +803,7 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
 template <typename T, int N, bool INV, int OP, int V>
 __global__ void __launch_bounds__((ColShape<T, N, V>::THREADS)) col_kernel(ColArgs<T> a) {
   __shared__ cx<T> lds_all[ColShape<T, N, V>::LDS];
-  if (a.skip && *a.skip != 0.0) return;  // Krylov iteration after convergence
+  if (block_skips(a.skip)) return;  // Krylov iteration after convergence
   int gx = gridDim.x, gy = gridDim.y;
   const int hw = blockIdx.x + gridDim.x * blockIdx.y;
   if constexpr (OP == COL_PLAIN) {
