@@ -238,15 +238,17 @@ __device__ __forceinline__ T precond_inv(T il, double dbar) {
 }
 
 // u = M^-1 r at one mode and its shares of (u^H Lambda^-1 u, r^H u, r^H r):
-// vector arithmetic in the Krylov vectors' precision, sums in FP64.
+// vector arithmetic in the Krylov vectors' precision, sums in FP64, and the
+// squares of r too: a right-hand side has the caller's scale, whose squares
+// FP32 need not hold (1e-24 squares to zero, 1e20 to infinity).
 template <typename T>
 __device__ __forceinline__ void cg_precondition(cx<T> r, T il, double dbar, double hw, cx<T>& u, double (&acc)[3]) {
   const T mi = precond_inv<T>(il, dbar);
   u = {mi * r.x, mi * r.y};
-  const T rr = r.x * r.x + r.y * r.y;
+  const double rr = (double)r.x * r.x + (double)r.y * r.y;
   acc[0] += hw * (double)(il * (u.x * u.x + u.y * u.y));
-  acc[1] += hw * (double)(mi * rr);
-  acc[2] += hw * (double)rr;
+  acc[1] += hw * ((double)mi * rr);
+  acc[2] += hw * rr;
 }
 
 // The step length of one iteration in the textbook order (two x passes per

@@ -962,6 +962,7 @@ int solve_spd(pl_plan* p, const pl_solve_opts& o, int* its_out, int* hv_out, dou
       its += it;
       hv += h;
       if (bnorm == 0.0) break;
+      if (!std::isfinite(bnorm)) break;  // nothing to relate the sweeps to (see rel_residual)
       hipLaunchKernelGGL((axpy_hat_kernel<float>), dim3(NB_RED), dim3(RED_THREADS), 0, p->stream, p->x64, p->x32,
                          1.0, p->Nh);
       HIPCHK(p, hipGetLastError());
@@ -988,6 +989,14 @@ int solve_spd(pl_plan* p, const pl_solve_opts& o, int* its_out, int* hv_out, dou
   *rres_out = rres;
   *bnorm_out = bnorm;
   return PL_OK;
+}
+
+// Final residual relative to the right-hand side (0 for a zero one).  A
+// right-hand side whose norm is not finite (in the Krylov vectors' precision)
+// has no solution to be near to.
+double rel_residual(double rres, double bnorm) {
+  if (!std::isfinite(bnorm)) return HUGE_VAL;
+  return bnorm > 0.0 ? rres / bnorm : 0.0;
 }
 
 template <typename T>
@@ -1019,7 +1028,7 @@ int adjoint_solve(pl_plan* p, const double* s_star, const double* dL_ds, double*
   inf.cg_its = its;
   inf.hvps = hv;
   inf.grad0 = bnorm;
-  inf.rel_grad = bnorm > 0.0 ? rres / bnorm : 0.0;
+  inf.rel_grad = rel_residual(rres, bnorm);
   double* lam = lambda_out ? lambda_out : p->rtmp;
   rc = inv_c2r<double>(p, p->x64, p->t64, lam);
   if (rc) return rc;
@@ -1204,7 +1213,7 @@ int lsq_solve(pl_plan* p, double* delta_out, const pl_solve_opts& o, pl_solve_in
   inf.cg_its = its;
   inf.hvps = hv;
   inf.grad0 = bnorm;
-  inf.rel_grad = bnorm > 0.0 ? rres / bnorm : 0.0;
+  inf.rel_grad = rel_residual(rres, bnorm);
   inf.status = inf.rel_grad > o.rtol ? PL_ERR_NOT_CONVERGED : PL_OK;
   if (inf.status) p->err = "LSQ solve stopped above the tolerance";
   if (info) *info = inf;

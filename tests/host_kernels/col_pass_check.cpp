@@ -5,7 +5,9 @@
 // different times has to decide as one: here the flag is set after the first of
 // its waves has read it, in both orders of waves, and the vectors must stay as
 // they were.  The iteration before it leaves its sums in workgroup memory, as
-// on the GPU.  Prints one line per case; exit status 1 on a failure.
+// on the GPU.  And the start pass (COL_CG_INIT) forms its sums in 64 bits from
+// right-hand sides of any scale that FP32 vectors hold.  Prints one line per
+// case; exit status 1 on a failure.
 #include "pl_kernels.hpp"
 
 #include <algorithm>
@@ -136,7 +138,29 @@ void check(const char* name, const std::vector<int>& order) {
               kept ? "kept" : "changed", (int)ok);
 }
 
+// r^H M^-1 r and r^H r of the start pass against sums of the same FP32 vectors
+// in 64 bits; M^-1 carries FP32's rounding (a few 2^-24)
+void check_start(double scale) {
+  Pass<float> s;
+  s.scal[SC_DBAR] = 0.5;
+  s.a.in = nullptr;
+  s.a.cg_rhs_sign = scale;
+  s.a.skip = nullptr;
+  launch<float, true, COL_CG_INIT>(s, {0, 1, 2, 3}, -1);
+  double rz = 0.0, rr = 0.0;
+  for (int i = 0; i < NH; ++i) {
+    const double hw = (i % H == 0 || i % H == H - 1) ? 1.0 : 2.0, x = s.r[i].x, y = s.r[i].y;
+    rr += hw * (x * x + y * y);
+    rz += hw * (x * x + y * y) / ((double)s.tab[i] + 0.5);
+  }
+  const double e1 = std::fabs(s.part_out[1] / rz - 1.0), e2 = std::fabs(s.part_out[2] / rr - 1.0);
+  const bool ok = rr > 0.0 && std::isfinite(rr) && e1 < 4e-7 && e2 < 1e-13;
+  g_ok = g_ok && ok;
+  std::printf("start scale %g: r^H r %g (error %.1e, r^H M^-1 r %.1e) ok=%d\n", scale, s.part_out[2], e2, e1, (int)ok);
+}
+
 int main() {
+  for (double scale : {1.0, 1e-24, 1e-30, 1e20, 1e30}) check_start(scale);
   for (const std::vector<int>& order : {std::vector<int>{0, 1, 2, 3}, std::vector<int>{3, 2, 1, 0}}) {
     check<double, false, COL_CG_STEP>("one-pass x pass FP64", order);
     check<float, false, COL_CG_LAST>("last x pass FP32", order);

@@ -31,3 +31,8 @@ def test_a_workgroup_decides_the_end_of_a_solve_as_one(lines):
     # orders: the vectors of the finished solve stay as they were
     ends = [l for l in lines if l.startswith("end ")]
     assert len(ends) == 8 and all(l.endswith("ok=1") for l in ends), "\n".join(lines)
+
+
+def test_the_start_pass_sums_squares_in_64_bits(lines):
+    starts = [l for l in lines if l.startswith("start ")]
+    assert len(starts) == 5 and all(l.endswith("ok=1") for l in starts), "\n".join(lines)
