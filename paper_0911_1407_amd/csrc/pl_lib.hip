@@ -486,7 +486,8 @@ int ensure_d32(pl_plan* p) {
 //   x pass:       x forward, p = u + beta p, y = F[d v] + beta y (y: the
 //                 diagonal part of H p, so H p = y + p/lambda), x += alpha p,
 //                 r -= alpha H p, u = M^-1 r, sums, x inverse of u
-// FP32 vectors, two x passes (the textbook order):
+// FP32 vectors, and FP64 solves to the last digits (kOnePassRtol), two x passes
+// (the textbook order):
 //   first x pass: p = M^-1 r + beta p, x inverse; partial p^H Lambda^-1 p
 //   z part:       on p
 //   last x pass:  x forward, r -= alpha (F[d v] + p/lambda), x += alpha p; sums
@@ -522,10 +523,20 @@ int next_cg_chunk(const double* sc, int check_every) {
 // pass's sums give on the device.  first_chunk (> 0) sets how many iterations
 // are queued before the first host check; later chunks are sized from the
 // residual decrease so far (next_cg_chunk).
+// FP64 solves to a tolerance below kOnePassRtol of the right-hand side (or to
+// none) keep the two x passes: over thousands of iterations the recurrence for
+// y and alpha's difference give up the last digits.  Against refined solutions,
+// one pass / two: at 1e-10 and 1e-12 the errors are equal (40 problems of 150 to
+// 22000 iterations), but on steep biases the residual reached at 1e-12 is up to
+// twice as large (2.0e-11 / 9.8e-12), and at 1e-14 the error 3 to 8 times (32^3
+// 1.2e-11 / 2.5e-12, 12 x 96 x 256 6.0e-11 / 7.4e-12).  Newton steps ask for
+// far less.
+constexpr double kOnePassRtol = 1e-10;
+
 template <typename T>
 int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double tol_rel_of_rhs, int max_cg,
         int check_every, int* its, int* hvps, double* rel_res, double* rhs_norm, int first_chunk = 0) {
-  constexpr bool kOnePass = sizeof(T) == 8;
+  const bool one_pass = sizeof(T) == 8 && (tol_abs > 0.0 || tol_rel_of_rhs >= kOnePassRtol);
   cx<T>*x = View<T>::x(p), *r = View<T>::r(p), *pp = View<T>::pv(p), *t = View<T>::t(p);
   const double invN = 1.0 / (double)p->N;
   const double* skip = p->scal + SC_DONE;
@@ -550,7 +561,7 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
     c.partials = part_x[0];
     c.cg_rhs = rhs;
     c.cg_rhs_sign = sign;
-    c.cg_p = kOnePass ? nullptr : pp;
+    c.cg_p = one_pass ? nullptr : pp;
     HIPCHK(p, run_col<T>(p, 0, true, COL_CG_INIT, c, &nbx));
   }
   int launched = 0;
@@ -562,8 +573,8 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
     for (int i = 0; i < chunk; ++i) {
       const int k = launched + i;  // iterations before this one
       // the x pass's sums that the scalars of this iteration come from
-      double* part_in = kOnePass ? part_x[k & 1] : part_x[0];
-      if (!kOnePass && k > 0) {
+      double* part_in = one_pass ? part_x[k & 1] : part_x[0];
+      if (!one_pass && k > 0) {
         ColArgs<T> c = cx0;
         c.in = pp;
         c.beta_part = part_x[1];
@@ -589,16 +600,18 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
       } else {
         // the iteration's scalars, by an extra workgroup of the y pass
         // (which does not need them; the x pass does)
-        const int kind = kOnePass ? FIN_CG_STEP : (k == 0 ? FIN_CG_ALPHA_FIRST : FIN_CG_ALPHA_K);
+        const int kind = one_pass ? FIN_CG_STEP : (k == 0 ? FIN_CG_ALPHA_FIRST : FIN_CG_ALPHA_K);
         const FinArgs fin{part_z, 0, 2, kind, k, 1.0, p->scal, (double)max_cg, part_in, nbx, invN};
         rc = run_yz<T>(p, ROW_HVP, t, ra, &nbz, &fin);
         if (rc) return rc;
       }
-      if constexpr (kOnePass) {
-        c.cg_p = pp;
-        c.cg_y = p->y64;
-        c.partials = part_x[(k + 1) & 1];
-        HIPCHK(p, run_col<T>(p, 0, false, COL_CG_STEP, c, &nbx));
+      if (one_pass) {
+        if constexpr (sizeof(T) == 8) {
+          c.cg_p = pp;
+          c.cg_y = p->y64;
+          c.partials = part_x[(k + 1) & 1];
+          HIPCHK(p, run_col<T>(p, 0, false, COL_CG_STEP, c, &nbx));
+        }
       } else {
         c.base = pp;
         c.partials = part_x[1];
@@ -606,7 +619,7 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
       }
     }
     launched += chunk;
-    if (kOnePass)
+    if (one_pass)
       HIPCHK(p, finalize(p, nbx, 3, FIN_CG_CHECK, launched, invN, (double)max_cg, part_x[launched & 1]));
     else
       HIPCHK(p, finalize(p, nbx, 2, FIN_CG_BETA_K, launched, invN, (double)max_cg, part_x[1]));
@@ -615,8 +628,8 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
     if (p->h_scal[SC_DONE] != 0.0) break;
   }
   *its = (int)p->h_scal[SC_ITS];
-  if constexpr (kOnePass) {
-    if (*its == 0 || (*its & 1)) {
+  if constexpr (sizeof(T) == 8) {
+    if (one_pass && (*its == 0 || (*its & 1))) {
       hipLaunchKernelGGL(cg_flush_kernel, dim3(NB_RED), dim3(RED_THREADS), 0, p->stream, x, pp, p->scal, p->Nh);
       HIPCHK(p, hipGetLastError());
     }
