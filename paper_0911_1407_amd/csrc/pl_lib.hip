@@ -147,12 +147,14 @@ size_t carve(pl_plan* p, char* base) {
   p->r64 = (cx<double>*)take(c64);
   p->p64 = (cx<double>*)take(c64);
   p->t64 = (cx<double>*)take(c64);
-  p->y64 = (cx<double>*)take(c64);
   p->s_ws = (double*)take(r64);
   p->e = (double*)take(r64);
   p->d = (double*)take(r64);
   p->preal = (double*)take(r64);
   p->rtmp = (double*)take(r64);
+  // the one-pass CG's y lies over preal and rtmp (together 16 N bytes, y 16 Nh
+  // with Nh = N / 2 + N / nz): neither is in use while a CG runs
+  p->y64 = (cx<double>*)p->preal;
   p->tab_mode = (double*)take(sizeof(double) * p->Nh);
   p->rad_len = (long)(p->n[0] / 2) * (p->n[0] / 2) + (long)(p->n[1] / 2) * (p->n[1] / 2) +
                (long)(p->n[2] / 2) * (p->n[2] / 2) + 1;
