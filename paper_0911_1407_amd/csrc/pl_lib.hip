@@ -1971,7 +1971,8 @@ extern "C" int pl_plan_autotune(pl_plan* p, const char* cache_path) {
   const std::string base = arch_name() + " " + std::to_string(p->n[0]) + "x" + std::to_string(p->n[1]) + "x" +
                            std::to_string(p->n[2]) + (p->radial ? " shell" : " mode");
   bool added = false;
-  rc = tune_precision<double>(p, base + " fp64", lines, &added);
+  // (lines keyed plain "fp64" were timed on the two-pass CG step)
+  rc = tune_precision<double>(p, base + " fp64-onepass", lines, &added);
   if (rc) return rc;
   if (p->precision == PL_MIXED) {
     rc = ensure_d32(p);
