@@ -353,13 +353,46 @@ int read_scalars(pl_plan* p) {
   return PL_OK;
 }
 
+// The fewest x planes for which a plane pass is the faster form of operation op.
+// A plane takes as long alone as beside 255 others, where separate passes spread
+// few planes over all CUs.  That matters for the planes whose waves take more
+// than one round on both axes (and 256 rows, four columns a wave): an operation
+// that runs one half of the pass (real rows at one end) then replaces two short
+// launches, one from half rows to half rows three.  Measured at 8 to 256 planes,
+// us of an operator with the separate passes / with plane passes:
+// - two halves (pl_hessvec, FP64): 256 x 64 27.9 / 31.2 at 16 planes, 39.8 / 40.9
+//   at 48, 41.3 / 39.4 at 64; 64 x 192 31.5 / 32.4 at 32, 40.3 / 38.6 at 48;
+//   96 x 192 49.3 / 55.0 at 64; FP32 256 x 128 34.0 / 41.1 at 32, 57.7 / 52.8 at
+//   96; 192 x 192 61.1 / 63.9 at 96, 76.7 / 66.1 at 128; 256 x 64 23.9 / 25.2 at
+//   16, 25.3 / 25.9 at 32.
+// - a whole one (pl_hessvec_hat, FP64): 256 x 64 23.9 / 25.0 at 8, 27.7 / 28.2 at
+//   16, 31.6 / 30.2 at 32; 96 x 192 44.1 / 46.0 at 48, 47.8 / 47.2 at 64; FP32
+//   256 x 128 32.4 / 34.0 at 32, 39.6 / 38.7 at 48; 192 x 192 44.0 / 46.8 at 48.
+// - with the gradient's exponentials (pl_grad): 128 x 128 41.0 / 42.8 at 16, 49.4 /
+//   47.2 at 32; 192 x 64 44.2 / 46.9 at 64.
+int plane_min_planes(int ny, int nz, bool fp64, int op) {
+  const bool whole = row_from_half(op) && row_to_half(op);
+  const bool exps = op == ROW_C2R_GRADLIK || op == ROW_GRAD_STEP;
+  const int cells = ny * nz;
+  if (plane_rounds(ny, nz) < 4 && !(ny == 256 && cells >= 12288)) return exps && cells >= 16384 ? 32 : 1;
+  if (fp64) {
+    if (exps) return 96;
+    if (cells >= 18432) return whole ? 64 : 96;
+    return whole ? 16 : (cells >= 16384 ? 64 : 48);
+  }
+  if (cells < 18432) return !whole && cells >= 16384 ? 32 : 1;
+  if (cells < 36864) return whole ? 48 : 96;
+  return whole ? 64 : 128;
+}
+
 // Whether the y and z passes of this grid run as one plane pass.
 template <typename T>
 bool use_plane(const pl_plan* p, int op) {
+  const int ny = p->n[1], nz = p->n[2];
   if ((op == ROW_GRAD || op == ROW_GRAD_STEP) && p->model == MODEL_GAUSSIAN) return false;
   // (its two diagonals spilled registers beside the longer bodies of class 1)
-  if (op == ROW_LB_IN && plane_class(p->n[1], p->n[2]) != 0) return false;
-  return plane_fits(p->n[1], p->n[2], (int)sizeof(cx<T>));
+  if (op == ROW_LB_IN && plane_class(ny, nz) != 0) return false;
+  return plane_fits(ny, nz, (int)sizeof(cx<T>)) && p->n[0] >= plane_min_planes(ny, nz, sizeof(T) == 8, op);
 }
 
 // The y and z passes of an operator on the half spectrum buf (in place): y
@@ -1741,6 +1774,14 @@ int plane_waves(int ny, int nz) {
   plane_groups(ny, nz, &cols, &rows);
   const int groups = std::max(cols, rows), rounds = (groups + PLANE_MAX_WAVES - 1) / PLANE_MAX_WAVES;
   return (groups + rounds - 1) / rounds;
+}
+
+// Rounds that the waves of a plane pass take over its columns and its row pairs.
+int plane_rounds(int ny, int nz) {
+  int cols, rows;
+  plane_groups(ny, nz, &cols, &rows);
+  const int w = plane_waves(ny, nz);
+  return (cols + w - 1) / w + (rows + w - 1) / w;
 }
 
 bool supported_length(int n) {

@@ -13,8 +13,8 @@
 // of 40000), a batch by how many planes a CU holds.  Measured, us per Hessian
 // product before (five passes) and now: 24^3 28.1 / 16.8, 32^3 22.6 / 14.9, 64^3
 // 25.9 / 18.3, 96^3 45.6 / 35, 128^3 59.5 / 43.8, 128^3 FP32 47.8 / 33.5,
-// 192^3 FP32 109 / 68, 64 x 192 x 96 51.5 / 48.4; 16 planes of 128 x 128 31.6 /
-// 28.5, the narrowest gain found, so every plane that fits is taken.
+// 192^3 FP32 109 / 68, 64 x 192 x 96 51.5 / 48.4.  Where few of the largest
+// planes leave most CUs idle the separate passes are faster (plane_min_planes).
 //
 // Work split: a wave owns 64 / P whole transforms (P threads each, P divides
 // 64 for every length), so the exchanges between radix stages stay inside one
@@ -293,6 +293,7 @@ constexpr bool plane_fits(int ny, int nz, int elem) {
 }
 void plane_groups(int ny, int nz, int* cols, int* rows);
 int plane_waves(int ny, int nz);
+int plane_rounds(int ny, int nz);
 
 inline bool plane_len_c0(int n) { return n == 32 || n == 48 || n == 64 || n == 96; }
 inline int plane_class(int ny, int nz) { return plane_len_c0(ny) && plane_len_c0(nz) ? 0 : 1; }
