@@ -610,13 +610,13 @@ __device__ __forceinline__ void col_body(const ColArgs<T>& a, int tile, int slab
     // last two directions are both at hand (p_old is read, p is formed), which
     // saves its read and write on the others.  Then u = M^-1 r of the new
     // residual, its sums and its inverse transform.
-    int k = a.cg_k;
-    if constexpr (BATCHED) k = (int)a.scal[SC_ITS];
+    static_assert(!BATCHED, "batches run the two-pass CG");
+    const int k = a.cg_k;
     double alpha, beta;
     if (a.z_part) {
       double dv[2], uv[3];
-      col_sums<T, N, V, BATCHED, 2>(a.z_part, a.z_nb, dv);
-      col_sums<T, N, V, BATCHED, 3>(a.beta_part, a.beta_nb, uv);
+      col_sums<T, N, V, false, 2>(a.z_part, a.z_nb, dv);
+      col_sums<T, N, V, false, 3>(a.beta_part, a.beta_nb, uv);
       const double delta = uv[0] * a.beta_scale + dv[0], gamma = uv[1] * a.beta_scale, rr = uv[2] * a.beta_scale;
       double* sc = const_cast<double*>(a.scal);
       const bool over = block_linear == 0 && threadIdx.x == 0
