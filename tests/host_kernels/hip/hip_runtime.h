@@ -2,8 +2,9 @@
 // a time, its lanes as cooperating fibers of one OS thread.  A lane runs until
 // it meets a workgroup barrier or a cross-lane exchange; lanes that have
 // returned do not hold a barrier up (the hardware counts live waves only).
-// Workgroup memory is static, so it keeps what the last workgroup left there,
-// as LDS does.
+// Workgroup memory belongs to the thread, so it keeps what the last workgroup
+// left there, as LDS does.  Between two barriers or exchanges a lane runs by
+// itself, so lanes that relied on running in step would be found out.
 #pragma once
 #include <ucontext.h>
 
@@ -20,7 +21,8 @@
 #define __global__
 #define __forceinline__ inline
 #define __launch_bounds__(...)
-#define __shared__ static
+#define __shared__ thread_local
+#define __align__(n) __attribute__((aligned(n)))
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
 
 struct HostDim {
@@ -62,10 +64,10 @@ inline void run_block(int n, const std::vector<int>& order, const std::function<
   body = &f;
   blockDim = {(unsigned)n, 1, 1};
   for (int i = 0; i < n; ++i) {
-    ls[i].stack.reset(new char[1 << 18]);
+    ls[i].stack.reset(new char[1 << 17]);
     getcontext(&ls[i].ctx);
     ls[i].ctx.uc_stack.ss_sp = ls[i].stack.get();
-    ls[i].ctx.uc_stack.ss_size = 1 << 18;
+    ls[i].ctx.uc_stack.ss_size = 1 << 17;
     ls[i].ctx.uc_link = nullptr;
     makecontext(&ls[i].ctx, entry, 0);
   }
@@ -120,6 +122,18 @@ T exchange(T v, int src) {
 }
 
 }  // namespace hostgpu
+
+#define __builtin_amdgcn_fence(...) ((void)0)
+#define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __builtin_amdgcn_wave_barrier() hostgpu::yield(hostgpu::AT_WAVE)
+
+struct int4 {
+  int x, y, z, w;
+};
+template <typename T>
+constexpr T min(T a, T b) {
+  return b < a ? b : a;
+}
 
 inline void __syncthreads() { hostgpu::yield(hostgpu::AT_BLOCK); }
 template <typename T>
