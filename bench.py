@@ -116,11 +116,11 @@ def linear_bias_hvp_bytes(n, lognormal):
 
 
 def cg_step_bytes(n, p):
-    """Algorithmic bytes of one fused CG step (five passes with the Krylov
-    updates): p N + 32 p Nh."""
+    """Algorithmic bytes of one CG step of a batch, x pass (8 p Nh), plane pass
+    (y, z, y: p N + 4 p Nh), x pass (12 p Nh): p N + 24 p Nh."""
     N = n[0] * n[1] * n[2]
     Nh = n[0] * n[1] * (n[2] // 2 + 1)
-    return p * N + 32 * p * Nh
+    return p * N + 24 * p * Nh
 
 
 def batched_workload(dev, rtol):
