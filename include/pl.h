@@ -101,7 +101,11 @@ typedef struct pl_solve_opts {
 typedef struct pl_solve_info {
   int newton_its;  /* Newton iterations taken */
   int cg_its;      /* CG iterations that changed the iterate */
-  int hvps;        /* Hessian-vector products launched (>= cg_its) */
+  int hvps;        /* Hessian-vector products of the solve (>= cg_its): one per
+                      CG iteration, one more where a CG broke down or began
+                      below its absolute tolerance, and those of refinements.
+                      The FP64 CG finds its end one product late; that last
+                      product is launched but not counted */
   int status;      /* same as the return code */
   double rel_grad; /* final ||g|| / ||g0|| (adjoint: final ||r|| / ||b||) */
   double grad0;    /* ||g(s0)|| (adjoint: ||b||) */
@@ -183,7 +187,10 @@ int pl_newton_krylov_solve_hat(pl_plan* plan, double* s_inout, double* s_hat_out
      dL/dnbar = -lambda^T (beta w e^{beta s})                   -> *dL_dnbar (host, nullable)
      dL/dN_i  = beta lambda_i                                    -> dL_dN     (device, N, nullable)
      dL/dw_i  = -lambda_i beta nbar e^{beta s_i}                 -> dL_dw     (device, N, nullable)
-   (implicit differentiation of g(s*; theta) = 0: dL/dtheta = -lambda^T dg/dtheta). */
+   (implicit differentiation of g(s*; theta) = 0: dL/dtheta = -lambda^T dg/dtheta).
+   PL_ERR_NOT_CONVERGED if max_cg ends the solve above rtol (the outputs are
+   still written), or if the spectrum of dL_ds exceeds the Krylov vectors'
+   precision (FP32 in a PL_MIXED solve). */
 int pl_solve_adjoint(pl_plan* plan, const double* s_star, const double* dL_ds, double* lambda_out,
                      double* dL_dA, double* dL_dbeta, double* dL_dnbar, double* dL_dN, double* dL_dw,
                      const pl_solve_opts* opts, pl_solve_info* info);
@@ -345,7 +352,12 @@ const char* pl_last_error(const pl_plan* plan);
    imaginary parts through LDS in turn, half the LDS and so more blocks per
    CU; 4 extra wide: 1024 threads, <= 160 KB LDS; 5 wide split: 512 threads,
    split exchanges in <= 64 KB; 6 extra-wide split: 1024 threads, split
-   exchanges in <= 128 KB) and the row (z) pass two (0, 1).
+   exchanges in <= 128 KB) and the row (z) pass two (0, 1).  For x axes of
+   32 to 128 points variant 0 is the default tile or a narrower one (128 or
+   64 threads), by the number of columns.  Where an operation runs its y and
+   z transforms as one pass per x plane (planes up to about 128 x 128 in FP64
+   and 192 x 192 in FP32, if there are enough of them) the y and z choices
+   select nothing for it.
    The x passes that apply 1/lambda read it from the per-mode table (0),
    or, when pl_plan_prior_is_radial, from the radial shell table (1) or
    from the per-mode table at (min(kx, nx - kx), ky, kz) (2, "mirror"): the
@@ -355,17 +367,19 @@ const char* pl_last_error(const pl_plan* plan);
    Hessian diagonal, the per-mode table) can be loaded, and the Krylov
    vectors stored, non-temporally so that the pass-to-pass intermediate
    stays in the memory-side cache, which pays when that intermediate fits
-   there.  Times the solver's fused CG step (five passes) per combination of
-   the Krylov-carrying x variant, the y and z variants and the Krylov
-   passes' table, then per streaming policy with those fixed, then the
+   there.  Times the solver's fused CG step (in FP64 one x pass and the y, z
+   and y passes or a plane pass; in FP32 two x passes) per combination of
+   the Krylov-carrying x variant, the y and z variants (where they select
+   something) and the Krylov passes' table, then per streaming policy with those fixed, then the
    tile and table choices again under that policy, then the
    isolated operator (pl_hessvec_hat) per
    combination of its own x variant and table, on the plan's workspace (after
    pl_set_problem; it overwrites the cached Hessian diagonal and the solver's
    Krylov vectors), and keeps the fastest, per precision.  Every choice
    gives the same result up to rounding.  cache_path (nullable): a text file
-   of earlier results keyed by arch, grid, table availability and precision;
-   entries found there are used without timing, new ones are appended. */
+   of earlier results keyed by arch, grid, table availability and precision
+   (FP64: the CG step timed, fp64-onepass); entries found there are used
+   without timing, new ones are appended. */
 int pl_plan_autotune(pl_plan* plan, const char* cache_path);
 
 /* Number of schedule choices per precision.  In order: x variant of the
@@ -414,16 +428,17 @@ int pl_batch_set_workspace(pl_batch* batch, void* dev_ptr);
 int pl_batch_set_problem(pl_batch* batch, int i, const pl_problem* prob);
 /* Tile schedules of the batched passes, picked per grid length by timing
    (the batch's counterpart of pl_plan_autotune).  For each distinct length
-   (the lengths holding the most cells first) the column passes and the row
-   pass of the instances of that length each take the default tile
-   (256 threads, <= 64 KB of LDS) or the narrow one (128 threads,
-   <= 32 KB; fewer idle lanes on short columns), whichever makes the
-   batched CG step (seven launches over every instance) fastest; FP64 and,
-   for a PL_MIXED batch, FP32.  Every launch then takes the largest block
-   and LDS of the instances it covers.  Needs every problem set; overwrites
+   (the lengths holding the most cells first) the x passes of the instances
+   whose x axis has that length take the default tile (256 threads, <= 64 KB
+   of LDS) or the narrow one (128 threads, <= 32 KB; more blocks for few
+   columns), whichever makes the batched CG step (three launches per length
+   class over every instance: x, plane, x) fastest; FP64 and, for a PL_MIXED
+   batch, FP32.  Every launch then takes the largest block and LDS of the
+   instances it covers.  Needs every problem set; overwrites
    the instances' Hessian diagonals and Krylov vectors.  cache_path
    (nullable): a text file of earlier results keyed by arch, precision and
-   the set of lengths, read and extended as for pl_plan_autotune.  Every
+   the set of lengths, read and extended as for pl_plan_autotune (each line's
+   second list of variants, once the row passes', is not used).  Every
    choice gives the same result up to rounding.  Synchronises. */
 int pl_batch_autotune(pl_batch* batch, const char* cache_path);
 /* s_inout: host array of n_inst device pointers (start on input, MAP on

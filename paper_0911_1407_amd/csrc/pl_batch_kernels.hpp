@@ -45,8 +45,9 @@ inline BatchShape<T> batch_shape(int n, int v) {
   }
 }
 
-// work item: (instance, tile, slab, block index in the instance); cls: the length class of every item of the launch (batch_class);
-// threads / lds_bytes: the launch's block size and dynamic LDS
+// work item: (instance, tile, slab, block index in the instance); cls: the length
+// class of every item of the launch (batch_class); threads / lds_bytes: the
+// launch's block size and dynamic LDS
 template <typename T>
 hipError_t launch_col_batch(bool inverse, int op, int cls, const ColArgs<T>* args, const int4* work, int nblocks,
                             int threads, int lds_bytes, hipStream_t st);

@@ -528,15 +528,21 @@ int ensure_d32(pl_plan* p) {
 //   last x pass:  x forward, r -= alpha (F[d v] + p/lambda), x += alpha p; sums
 // The single pass saves a launch, a table and, adding x's two last steps at
 // once, one of 16 half-spectrum transfers (256^3 FP64: 436 -> 414 us per
-// iteration; 96^3 adjoint solve 12.1 -> 9.9 ms; same iteration counts).  In
-// FP32 the recurrence for y loses what the textbook order recomputes: a 128^3
-// solve took 798 iterations instead of 476.
+// iteration; 96^3 adjoint solve 12.1 -> 9.9 ms; on steep biases rounding costs it
+// 1-8% more iterations, for 5-14% less time: 256^3 with a bias of 1.5 to 1e-10
+// 4526 in 1971 ms against 4371 in 2027 ms).  In FP32 the recurrence for y loses
+// what the textbook order recomputes: a 128^3 solve took 798 iterations instead
+// of 476.
 // alpha = -(xi^T grad Q)/(xi^T H xi) is the step of eq. (New5) for the local
-// quadratic model (xi = p).  The scalars are formed by every workgroup of the x
-// pass that needs them after a plane pass (at most about 260 + 256 partial sums),
-// by an extra workgroup of the y forward pass otherwise.  Iterations queued
-// after convergence exit at once on the device (the passes read the done flag).
-// *its receives iterations that changed x, *hvps the Hessian products run.
+// quadratic model (xi = p).  After a plane pass every workgroup of the x pass that
+// needs the scalars forms them, from a record per x tile and plane (520 + 128 at
+// 128^3, 1040 + 512 at 512 x 128 x 128); a launch of its own for that measured
+// slower or, at most, equal (us per FP64 iteration without / with it: 32^3 21.1 /
+// 25.9, 128^3 57.6 / 62.9, 512 x 128 x 128 236.4 / 236.4).  Otherwise an extra
+// workgroup of the y forward pass forms them.  Iterations queued after convergence
+// exit at once on the device (the passes read the done flag).
+// *its receives iterations that changed x, *hvps the Hessian products behind them
+// (see pl_solve_info).
 // ---------------------------------------------------------------------------
 // CG iterations to queue after a host check found the solve still running:
 // the residual fell from rr0 to rr in its iterations, so at that rate it
@@ -669,10 +675,10 @@ int pcg(pl_plan* p, const cx<double>* rhs, double sign, double tol_abs, double t
       HIPCHK(p, hipGetLastError());
     }
   }
-  // Hessian products that ran: one per counted iteration, plus the partial
-  // one of a breakdown (or of a first iteration whose residual was already
-  // below an absolute tolerance); queued iterations after convergence exit
-  // at once
+  // one product per counted iteration, plus the partial one of a breakdown or of
+  // a first residual below an absolute tolerance.  The one-pass form finds its
+  // end behind the z part of the next product, which is not counted; iterations
+  // queued after that exit at once
   *hvps = *its + ((p->h_scal[SC_DONE] == 2.0 || (!(tol_rel2 > 0.0) && *its == 0)) ? 1 : 0);
   if (rel_res) *rel_res = std::sqrt(std::max(0.0, p->h_scal[SC_RR]));
   if (rhs_norm) *rhs_norm = std::sqrt(p->h_scal[SC_RR0]);
@@ -1809,9 +1815,7 @@ std::string arch_name() {
   return c == std::string::npos ? a : a.substr(0, c);
 }
 
-// Time one fused CG step (the solver's hot loop: the z part and the x passes
-// with the Krylov updates), average of `reps`, with the plan's current variants.  Runs on zeroed vectors with
-// zero step lengths, so nothing is left in a meaningful state.
+// Hashed values for the timing runs.
 template <typename T>
 int fill_hash(pl_plan* p, T* x, long n, unsigned seed, double lo = -1.0, double span = 2.0) {
   hipLaunchKernelGGL((fill_hash_kernel<T>), dim3(grid_blocks(n)), dim3(RED_THREADS), 0, p->stream, x, n, seed, lo,
@@ -1820,6 +1824,10 @@ int fill_hash(pl_plan* p, T* x, long n, unsigned seed, double lo = -1.0, double 
   return PL_OK;
 }
 
+// Time one fused CG step (the solver's hot loop: the z part and the x passes with
+// the Krylov updates), average of `reps`, with the plan's current variants.  Runs
+// on hashed vectors with zero step lengths, so nothing is left in a meaningful
+// state.
 template <typename T>
 int time_cg_step(pl_plan* p, int reps, float* ms) {
   cx<T>*x = View<T>::x(p), *r = View<T>::r(p), *pp = View<T>::pv(p), *t = View<T>::t(p);
@@ -2855,9 +2863,9 @@ int batch_newton(pl_batch* b, double* const* s_io, const pl_solve_opts& o, pl_so
   return first_bad;
 }
 
-// Time one batched CG step (the launches of bcg_chunk over every instance) with the current tile variants, average of `reps`; on hashed
-// Krylov vectors and Hessian diagonals, so nothing is left in a meaningful
-// state.
+// Time one batched CG step (the launches of bcg_chunk over every instance) with
+// the current tile variants, average of `reps`; on hashed Krylov vectors and
+// Hessian diagonals, so nothing is left in a meaningful state.
 template <typename T>
 int time_batch_cg(pl_batch* b, int reps, float* ms) {
   build_work(b);

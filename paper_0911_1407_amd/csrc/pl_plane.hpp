@@ -204,8 +204,9 @@ struct WaveRowFft {
 
 // y transforms of a plane, wave `wave` of `nwaves`.  INV: from the half
 // spectrum in memory into the plane in LDS; else from LDS to memory.  HC: the
-// half row's length where it is known at compile time (square planes), so that
-// every LDS access is one address and an instruction offset; else 0.
+// half row's length where it is known at compile time (square planes of 32 to 128
+// points, the cubes of common use), so that every LDS access is one address and an
+// instruction offset; else 0 (a body for every pair of lengths would be too many).
 template <typename T, int N, bool INV, int HC>
 __device__ __forceinline__ void plane_cols(const cx<T>* __restrict__ src, cx<T>* __restrict__ dst, cx<T>* plane,
                                            int h_, int pitch_, const cx<T>* __restrict__ tw, int wave, int nwaves) {
@@ -375,7 +376,8 @@ __global__ void __launch_bounds__((CLS == 0 ? 8 : PLANE_MAX_WAVES) * 64) plane_k
   if constexpr (row_has_sums(OP)) block_reduce_store<2>(acc, a.partials, blockIdx.x);
 }
 
-// Batched plane pass: a block takes up to `per` planes of one instance, w
+// Batched plane pass (named by its operation, one of the row pass's, like the
+// other batched kernels): a block takes up to `per` planes of one instance, w
 // waves each (planes of short rows would leave most of a block idle); work
 // item: (instance, first plane, w | per << 8, -).  The sums have a record per
 // plane, however the planes are split: a block's go to its first plane's, zeros
